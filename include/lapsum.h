@@ -82,9 +82,13 @@ const char* lapsum_status_string(int status);
  *            +0.0 precedes -0.0) and then by ascending original index.
  *            Asking for it makes the sort carry indices (slower).
  * Rows with n <= 32768 are solved by one workgroup per row entirely on chip,
- * except a batch of one row longer than 16384, which is faster through the
- * device-wide sort and scan; longer rows use the device-wide path, one row
- * after another.  The workspace size depends on batch for that reason.
+ * except a batch of one row longer than 16384.  That row and all longer ones
+ * are solved device-wide, several rows at a time, without sorting: a sample
+ * gives a window that holds b, one pass sums the scores outside it and keeps
+ * those inside, and the members around the root give the same b as the sort
+ * (they are sorted only for perm_out, one row after another).  The workspace
+ * size depends on batch for both reasons; it does not exceed the larger of
+ * one row's and 48 MiB.
  * ------------------------------------------------------------------------ */
 size_t lapsum_forward_workspace_size(int64_t batch, int64_t n, int with_perm);
 

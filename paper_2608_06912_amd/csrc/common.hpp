@@ -66,12 +66,47 @@ __device__ __forceinline__ void store_stream4(float* p, float4 x) {
   __builtin_nontemporal_store(v, reinterpret_cast<stream_v4f*>(p));
 }
 
+// Four scores at a 4-byte aligned address (rows of odd length): one 16-byte
+// load, which global memory serves at any 4-byte alignment.
+struct __attribute__((packed, aligned(4))) Quad {
+  float x, y, z, w;
+};
+__device__ __forceinline__ float4 load_quad(const float* p) {
+  const Quad q = *reinterpret_cast<const Quad*>(p);
+  return make_float4(q.x, q.y, q.z, q.w);
+}
+__device__ __forceinline__ void store_quad(float* p, float4 v) {
+  *reinterpret_cast<Quad*>(p) = Quad{v.x, v.y, v.z, v.w};
+}
+
 // e^{-d/t} for d >= 0 with the exponent formed in float64 (d may be the
 // difference of two float32 scores of very different size) and the
 // exponential in float32; c2 = log2(e)/t.  For per-score terms summed in
 // float64: each term carries one float32 rounding, never a product of them.
 __device__ __forceinline__ double wexp_f32(double d, double c2) {
   return static_cast<double>(exp2_fast(static_cast<float>(-d * c2)));
+}
+
+// 2^y for y <= 0 to about 1e-11 relative: 2^rint(y) times the Taylor
+// polynomial of 2^f = e^{f ln 2} to the ninth power, |f| <= 1/2 (remainder
+// (ln 2 / 2)^10 / 10! = 7e-12).  A row of few distinct values sums the same
+// term many times, so the one-ulp error of a float32 exponential would not
+// average out; about 30 cycles more per wave than that one.
+__device__ __forceinline__ double exp2_neg(double y) {
+  y = fmax(y, -2000.0);
+  const double n = rint(y);
+  const double f = y - n;
+  double r = 1.01780860092396960e-07;
+  r = fma(r, f, 1.32154867901443053e-06);
+  r = fma(r, f, 1.52527338040598377e-05);
+  r = fma(r, f, 1.54035303933816061e-04);
+  r = fma(r, f, 1.33335581464284411e-03);
+  r = fma(r, f, 9.61812910762847688e-03);
+  r = fma(r, f, 5.55041086648215762e-02);
+  r = fma(r, f, 2.40226506959100694e-01);
+  r = fma(r, f, 6.93147180559945286e-01);
+  r = fma(r, f, 1.0);
+  return ldexp(r, static_cast<int>(n));
 }
 
 // Laplace(0, t) draw number s of the bracket's default kernel noise (the

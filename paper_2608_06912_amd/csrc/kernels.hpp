@@ -165,9 +165,18 @@ hipError_t launch_dftopk_backward(const float* g, const float* p, int64_t n, con
 hipError_t launch_topk_mask(const int32_t* perm, int64_t batch, int64_t n, int64_t k, float* mask,
                             hipStream_t s);
 
-// Laplace-CDF emit p = sigma((r - b)/t) for one row, b read from device.
-hipError_t launch_emit(const float* r, int64_t n, const double* b_dev, double t, float* p,
-                       hipStream_t s);
+// Laplace-CDF emit p = sigma((r - b)/t) for `rows` consecutive rows of n
+// scores, b ([rows]) read from device.
+hipError_t launch_emit(const float* r, int64_t rows, int64_t n, const double* b_dev, double t,
+                       float* p, hipStream_t s);
+
+// Threshold of `rows` consecutive long rows without sorting them
+// (long_solve.hip), b[rows]; n >= 16385 (the sample's strata), rows <= 65535.
+// ws: long_solve_bytes(rows, n) bytes, 256-byte aligned, content irrelevant.
+constexpr int kLongMaxBlocks = 512;   // blocks a row's streaming pass takes
+size_t long_solve_bytes(int64_t rows, int64_t n);
+hipError_t launch_long_solve(const float* scores, int64_t rows, int64_t n, double k, double t,
+                             void* ws, double* b, hipStream_t s);
 
 // Device-wide backward for one row: partial sums per block, reduced in a
 // fixed order to coef[0] = <g, q> and coef[1] = 1/t (0 when sum f == 0),

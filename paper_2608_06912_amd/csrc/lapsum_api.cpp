@@ -112,17 +112,26 @@ int check_ws(void* ws, size_t have, size_t need) {
     if ((expr) != hipSuccess) return LAPSUM_ERR_HIP; \
   } while (0)
 
-// --------------------------------------------------- full-sort long rows --
+// ------------------------------------------------------------- long rows --
 struct FullWs {
-  SortBuffers sb;
-  int64_t solve_tiles;
-  double* tile_buf;
-  SolveRec* rec;
+  void* base;       // the long rows' solve works from here
+  SortBuffers sb;   // the permutation's sort, after the solve
 };
 
-FullWs carve_full(Carve& c, int64_t n, bool with_vals) {
+// Rows solved by one set of launches: as many as fit in kLongRowsBytes of
+// workspace (every row of a batch up to there, one row always).  The
+// workspace of a batch therefore stays within that bound or what one row's
+// sort takes, whichever is more.
+constexpr size_t kLongRowsBytes = size_t(48) << 20;
+
+int64_t long_rows(int64_t batch, int64_t n) {
+  int64_t rows = batch < 1024 ? batch : 1024;
+  while (rows > 1 && long_solve_bytes(rows, n) > kLongRowsBytes) rows -= (rows + 15) / 16;
+  return rows < 1 ? 1 : rows;
+}
+
+FullWs carve_full(Carve& c, int64_t batch, int64_t n, bool with_vals) {
   FullWs w{};
-  const int64_t tiles = tiles_of(n) < 1 ? 1 : tiles_of(n);
   w.sb.keys[0] = c.take<uint32_t>(n);
   w.sb.keys[1] = c.take<uint32_t>(n);
   w.sb.vals[0] = with_vals ? c.take<int32_t>(n) : nullptr;
@@ -130,36 +139,25 @@ FullWs carve_full(Carve& c, int64_t n, bool with_vals) {
   w.sb.hist = c.take<uint32_t>(sort_hist_words(n));
   w.sb.totals = c.take<uint32_t>(256);
   w.sb.max_tiles = sort_max_tiles(n);
-  w.solve_tiles = tiles;
-  w.tile_buf = c.take<double>(static_cast<size_t>(tiles) * kSolveTileDoubles);
-  w.rec = c.take<SolveRec>(1);
+  // (room that the size of a row's workspace has always counted)
+  c.take<double>(static_cast<size_t>(tiles_of(n) < 1 ? 1 : tiles_of(n)) * kSolveTileDoubles);
+  c.take<SolveRec>(1);
+  // the solve works in the same memory, before the sort
+  const size_t need = long_solve_bytes(long_rows(batch, n), n);
+  if (c.size() < need) c.take<char>(need - c.off);
+  w.base = w.sb.keys[0];
   return w;
 }
 
-// Sort one long row, solve for b (written to b_row), optionally copy the
-// permutation.  Does not emit.
-int full_row_solve(const float* r, int64_t n, double k, double t, double* b_row, int32_t* perm_row,
-                   FullWs& w, hipStream_t s) {
-  const uint32_t* keys = nullptr;
-  const int32_t* vals = nullptr;
-  LAPSUM_TRY(launch_sort(r, nullptr, nullptr, perm_row != nullptr, n, nullptr, w.sb, 0xfu, &keys,
-                         &vals, s));
-  SolveArgs a{};
-  a.keys = keys;
-  a.len = n;
-  a.len_dev = nullptr;
-  a.k = k;
-  a.t = t;
-  a.n_total = n;
-  a.tails = nullptr;
-  a.tile_buf = w.tile_buf;
-  a.max_tiles = w.solve_tiles;
-  a.out = w.rec;
-  a.b_out = b_row;
-  LAPSUM_TRY(launch_sorted_solve(a, s));
-  if (perm_row)
-    LAPSUM_TRY(hipMemcpyAsync(perm_row, vals, static_cast<size_t>(n) * sizeof(int32_t),
-                              hipMemcpyDeviceToDevice, s));
+// Solve `batch` long rows for b and emit p.
+int long_forward(const float* scores, int64_t batch, int64_t n, double k, double t, float* p,
+                 double* b, void* ws, hipStream_t s) {
+  const int64_t step = long_rows(batch, n);
+  for (int64_t row = 0; row < batch; row += step) {
+    const int64_t rows = batch - row < step ? batch - row : step;
+    LAPSUM_TRY(launch_long_solve(scores + row * n, rows, n, k, t, ws, b + row, s));
+    LAPSUM_TRY(launch_emit(scores + row * n, rows, n, b + row, t, p + row * n, s));
+  }
   return LAPSUM_OK;
 }
 
@@ -184,7 +182,7 @@ struct BracketWs {
   int64_t m_solve_tiles;
   double* m_tile_buf;
   SolveRec* rec;       // &att->rec
-  FullWs fall;         // full-sort fallback
+  void* fall;          // the long rows' solve, for rows without a certified bracket
   uint32_t* ones;      // [ceil(n/kBandTile) kBandTile/32] scores at or above the band (finite a_R)
   void* band;          // one row's band when the caller keeps none
   int nblocks;
@@ -229,7 +227,7 @@ BracketWs carve_bracket(Carve& c, int64_t n, int64_t K, int64_t mcap, bool with_
     w.m_tile_buf = c.take<double>(static_cast<size_t>(mt) * kSolveTileDoubles);
   }
   w.rec = w.att ? &w.att->rec : nullptr;
-  if (n > kRowOnChipMax) w.fall = carve_full(c, n, false);
+  w.fall = n > kRowOnChipMax ? c.take<char>(long_solve_bytes(1, n)) : nullptr;
   w.ones = c.take<uint32_t>(static_cast<size_t>((n + kBandTile - 1) / kBandTile * (kBandTile / 32)));
   w.band = c.take<char>(band_ctx_bytes(n));
   return w;
@@ -572,9 +570,8 @@ int bracketed_row(const float* r, int64_t n, double k, double alpha, int64_t K, 
       // the on-chip kernel also emits p
       LAPSUM_TRY(launch_row_forward(r, 1, n, k, t, p_row, b_row, nullptr, false, s));
     } else {
-      st = full_row_solve(r, n, k, t, b_row, nullptr, w.fall, s);
+      st = long_forward(r, 1, n, k, t, p_row, b_row, w.fall, s);
       if (st != LAPSUM_OK) return st;
-      LAPSUM_TRY(launch_emit(r, n, b_row, t, p_row, s));
     }
     LAPSUM_TRY(launch_ctx_dense(band, n, s));
   }
@@ -677,7 +674,7 @@ size_t lapsum_forward_workspace_size(int64_t batch, int64_t n, int with_perm) {
   if (n < 1) return 0;
   if (forward_on_chip(batch, n)) return 0;
   Carve c(nullptr);
-  carve_full(c, n, with_perm != 0);
+  carve_full(c, batch, n, with_perm != 0);
   return c.size();
 }
 
@@ -706,12 +703,16 @@ int lapsum_forward(const float* scores, int64_t batch, int64_t n, double k, doub
     return LAPSUM_OK;
   }
   Carve c(workspace);
-  FullWs w = carve_full(c, n, perm_out != nullptr);
+  FullWs w = carve_full(c, batch, n, perm_out != nullptr);
+  const int st = long_forward(scores, batch, n, k, t, p, b, w.base, stream);
+  if (st != LAPSUM_OK || !perm_out) return st;
   for (int64_t row = 0; row < batch; ++row) {
-    const float* r = scores + row * n;
-    int st = full_row_solve(r, n, k, t, b + row, perm_out ? perm_out + row * n : nullptr, w, stream);
-    if (st != LAPSUM_OK) return st;
-    LAPSUM_TRY(launch_emit(r, n, b + row, t, p + row * n, stream));
+    const uint32_t* keys = nullptr;
+    const int32_t* vals = nullptr;
+    LAPSUM_TRY(launch_sort(scores + row * n, nullptr, nullptr, true, n, nullptr, w.sb, 0xfu, &keys,
+                           &vals, stream));
+    LAPSUM_TRY(hipMemcpyAsync(perm_out + row * n, vals, static_cast<size_t>(n) * sizeof(int32_t),
+                              hipMemcpyDeviceToDevice, stream));
   }
   return LAPSUM_OK;
 }

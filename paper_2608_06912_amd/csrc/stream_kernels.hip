@@ -61,21 +61,23 @@ hipError_t launch_topk_mask(const int32_t* perm, int64_t batch, int64_t n, int64
 }
 
 // ------------------------------------------------------------------ emit ---
-__global__ __launch_bounds__(kStreamThreads) void emit_kernel(const float* __restrict__ r,
+// One row per grid.y.  16-byte accesses at any 4-byte alignment, so that the
+// rows of a batch of odd length take them too.
+__global__ __launch_bounds__(kStreamThreads) void emit_kernel(const float* __restrict__ scores,
                                                               int64_t n,
                                                               const double* __restrict__ b_dev,
                                                               double inv_t,
-                                                              float* __restrict__ p) {
-  const double b = *b_dev;
+                                                              float* __restrict__ probs) {
+  const int64_t row = blockIdx.y;
+  const float* r = scores + row * n;
+  float* p = probs + row * n;
+  const double b = b_dev[row];
   const int64_t base = static_cast<int64_t>(blockIdx.x) * kStreamTile;
   const int tid = threadIdx.x;
-  const bool vec = ((reinterpret_cast<uintptr_t>(r) | reinterpret_cast<uintptr_t>(p)) & 15) == 0;
-  if (vec && base + kStreamTile <= n) {
-    const float4* r4 = reinterpret_cast<const float4*>(r + base);
-    float4* p4 = reinterpret_cast<float4*>(p + base);
+  if (base + kStreamTile <= n) {
     float4 v[kStreamVec];
 #pragma unroll
-    for (int j = 0; j < kStreamVec; ++j) v[j] = r4[j * kStreamThreads + tid];
+    for (int j = 0; j < kStreamVec; ++j) v[j] = load_quad(r + base + 4 * (j * kStreamThreads + tid));
 #pragma unroll
     for (int j = 0; j < kStreamVec; ++j) {
       float4 o;
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(kStreamThreads) void emit_kernel(const float* __res
       o.y = laplace_p(v[j].y, b, inv_t);
       o.z = laplace_p(v[j].z, b, inv_t);
       o.w = laplace_p(v[j].w, b, inv_t);
-      p4[j * kStreamThreads + tid] = o;
+      store_quad(p + base + 4 * (j * kStreamThreads + tid), o);
     }
   } else {
     for (int64_t i = base + tid; i < n && i < base + kStreamTile; i += kStreamThreads)
@@ -91,12 +93,13 @@ __global__ __launch_bounds__(kStreamThreads) void emit_kernel(const float* __res
   }
 }
 
-hipError_t launch_emit(const float* r, int64_t n, const double* b_dev, double t, float* p,
-                       hipStream_t s) {
+hipError_t launch_emit(const float* r, int64_t rows, int64_t n, const double* b_dev, double t,
+                       float* p, hipStream_t s) {
+  if (rows < 1 || rows > 65535) return hipErrorInvalidValue;
   const int64_t blocks = (n + kStreamTile - 1) / kStreamTile;
   { ProfScope ps_("emit", s);
-  hipLaunchKernelGGL(emit_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kStreamThreads), 0, s,
-                     r, n, b_dev, 1.0 / t, p); }
+  hipLaunchKernelGGL(emit_kernel, dim3(static_cast<unsigned>(blocks), static_cast<unsigned>(rows)),
+                     dim3(kStreamThreads), 0, s, r, n, b_dev, 1.0 / t, p); }
   return hipGetLastError();
 }
 

@@ -1,0 +1,109 @@
+"""Long rows without a permutation (no sort: a sampled window, one streaming
+pass, the members around the root narrowed down) against the float64 oracle,
+at the sizes and on the score patterns where the path can go wrong: one to
+three scores past a quad, cells of equal members, blocks that outgrow their
+staging, unbounded windows, a sample that misleads, batches of odd length.
+"""
+import numpy as np
+import pytest
+
+import oracle.lapsum_oracle as O
+from test_gpu_parity import P_TOL, _np, _t, sum_tol
+
+pytestmark = pytest.mark.gpu
+
+
+def _row(dist, n, rng):
+    x = rng.standard_normal(n)
+    if dist == "levels":
+        x = rng.integers(0, 16, n) / 4.0
+    elif dist == "half_zero":      # half of the row is one value
+        x = np.maximum(x, 0.0)
+    elif dist == "narrow":         # far narrower than t: a wide share of the row in the window
+        x = 1.0 + 1e-3 * x
+    elif dist == "apart":          # every two scores many temperatures apart
+        x = rng.permutation(n).astype(np.float64)
+    elif dist == "sorted":
+        x = np.sort(x)
+    elif dist == "outliers":
+        x[:3] = [40.0, -1e30, 60.0]
+    elif dist == "constant":
+        x[:] = 0.75
+    return x.astype(np.float32)
+
+
+def _check(r, k, alpha, p, b, label):
+    t = -alpha
+    b_ref = O.solve_sorted_scan(r, k, alpha)
+    assert abs(b - b_ref) <= 2e-8 * t + 4e-16 * abs(b_ref), (label, b, b_ref)
+    p_ref = O.probs(r, b_ref, alpha)
+    assert float(np.max(np.abs(p.astype(np.float64) - p_ref))) <= P_TOL, label
+    assert O.budget_error(p, k) <= sum_tol(k), label
+
+
+@pytest.mark.parametrize("n", [16385, 16386, 16387, 20480, 32768, 40961, 262144 + 3])
+@pytest.mark.parametrize("dist", ["normal", "levels", "half_zero", "narrow", "apart", "sorted",
+                                  "outliers", "constant"])
+def test_long_row_against_oracle(lib, n, dist):
+    rng = np.random.default_rng([n, len(dist)])
+    r = _row(dist, n, rng)
+    x = _t(r)
+    for k, alpha in ((n / 2.0, -1.0), (16.0, -0.5), (7.0, -1e-3), (0.97 * n, -0.3), (n // 3, -0.01)):
+        p, b = lib.lapsum_forward(x, float(k), alpha)
+        _check(r, float(k), alpha, _np(p), float(_np(b)[0]), (n, dist, k, alpha))
+
+
+@pytest.mark.parametrize("n,frac", [((1 << 22) + 5, 0.01), ((1 << 22) + 5, 0.5), (6_000_001, 0.06)])
+def test_long_row_of_many_cells(lib, n, frac):
+    """Rows past 2^22 scores: 256 cells, merged by a launch of their own."""
+    rng = np.random.default_rng(n)
+    for dist in ("normal", "levels", "half_zero"):
+        r = _row(dist, n, rng)
+        p, b = lib.lapsum_forward(_t(r), frac * n, -0.5)
+        _check(r, frac * n, -0.5, _np(p), float(_np(b)[0]), (n, dist, frac))
+
+
+@pytest.mark.parametrize("batch,n", [(3, 32771), (70, 32769), (5, 400001)])
+def test_long_rows_of_a_batch(lib, batch, n):
+    rng = np.random.default_rng([batch, n])
+    r = np.stack([_row(("normal", "levels", "narrow")[i % 3], n, rng) for i in range(batch)])
+    p, b = lib.lapsum_forward(_t(r), n / 20.0, -0.1)
+    p, b = _np(p), _np(b)
+    for i in range(0, batch, max(1, batch // 6)):
+        _check(r[i], n / 20.0, -0.1, p[i], float(b[i]), (batch, n, i))
+
+
+def _sample_positions(n, m=4096):
+    """Where the window's sample reads (one hashed position per stratum)."""
+    s = np.arange(m, dtype=np.uint64)
+    a, e = s * n // m, (s + 1) * n // m
+    x = s.astype(np.uint32)
+    x ^= x >> np.uint32(16)
+    x *= np.uint32(0x7feb352d)
+    x ^= x >> np.uint32(15)
+    x *= np.uint32(0x846ca68b)
+    x ^= x >> np.uint32(16)
+    return (a + ((x.astype(np.uint64) * (e - a)) >> np.uint64(32))).astype(np.int64)
+
+
+@pytest.mark.parametrize("shift", [3.0, -3.0])
+def test_long_row_outside_its_window(lib, shift):
+    """Scores laid out so that the sample sees another distribution than the
+    row has: the root lies outside the window on either side, and the row is
+    narrowed whole."""
+    n = 50001
+    rng = np.random.default_rng(17)
+    r = rng.standard_normal(n).astype(np.float32)
+    r[_sample_positions(n)] += np.float32(shift)
+    for k, alpha in ((n / 2.0, -0.05), (500.0, -0.1)):
+        p, b = lib.lapsum_forward(_t(r), k, alpha)
+        _check(r, k, alpha, _np(p), float(_np(b)[0]), (shift, k, alpha))
+
+
+def test_long_row_is_deterministic(lib):
+    rng = np.random.default_rng(23)
+    for dist in ("normal", "levels"):
+        x = _t(_row(dist, 300_001, rng))
+        p1, b1 = lib.lapsum_forward(x, 3000.0, -0.2)
+        p2, b2 = lib.lapsum_forward(x, 3000.0, -0.2)
+        assert np.array_equal(_np(p1), _np(p2)) and np.array_equal(_np(b1), _np(b2))
