@@ -56,7 +56,8 @@ __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_ex
 // written by the band passes) use non-temporal accesses, so that they
 // neither evict nor leave behind dirty lines that the next pass would have
 // to write back.
-typedef float stream_v4f __attribute__((ext_vector_type(4)));
+// (any 4-byte alignment: the rows of a batch of odd length)
+typedef float stream_v4f __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ float4 load_stream4(const float* p) {
   const stream_v4f v = __builtin_nontemporal_load(reinterpret_cast<const stream_v4f*>(p));
   return make_float4(v.x, v.y, v.z, v.w);

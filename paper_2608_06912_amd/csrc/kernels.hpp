@@ -178,21 +178,21 @@ size_t long_solve_bytes(int64_t rows, int64_t n);
 hipError_t launch_long_solve(const float* scores, int64_t rows, int64_t n, double k, double t,
                              void* ws, double* b, hipStream_t s);
 
-// Device-wide backward for one row: partial sums per block, reduced in a
-// fixed order to coef[0] = <g, q> and coef[1] = 1/t (0 when sum f == 0),
-// then the emit.  The partials are (sum s, sum s g), or with grad_k /
+// Device-wide backward for `rows` consecutive rows of n: partial sums per
+// block, reduced in a fixed order to coef[0] = <g, q> and coef[1] = 1/t (0
+// when sum f == 0) of each row, then the emit.  The partials are (sum s, sum s g), or with grad_k /
 // grad_alpha requested (sum s, sum s g, sum s u, sum s g u) with
-// s = min(p, 1 - p), u = (r - b)/t; partials holds 4 doubles per block.
-// grad_k / grad_alpha: one float64 each (may be null).  With many partials
+// s = min(p, 1 - p), u = (r - b)/t; partials holds 4 doubles per block and
+// row, coef 2 per row.  grad_k / grad_alpha: [rows] float64 each (may be null).  With many partials
 // one block combines them into coef (launched by launch_vjp_reduce); with
 // few, every emit block combines them itself and coef is not used.  Both
 // calls take the same nblocks / nparts and grad_k / grad_alpha.
 int vjp_reduce_blocks(int64_t n);
-hipError_t launch_vjp_reduce(const float* g, const float* p, int64_t n, double* partials,
-                             int nblocks, double t, double* coef, double* grad_k,
+hipError_t launch_vjp_reduce(const float* g, const float* p, int64_t rows, int64_t n,
+                             double* partials, int nblocks, double t, double* coef, double* grad_k,
                              double* grad_alpha, hipStream_t s);
-hipError_t launch_vjp_emit(const float* g, const float* p, int64_t n, const double* coef,
-                           const double* partials, int nparts, double t, double* grad_k,
+hipError_t launch_vjp_emit(const float* g, const float* p, int64_t rows, int64_t n,
+                           const double* coef, const double* partials, int nparts, double t, double* grad_k,
                            double* grad_alpha, float* grad, hipStream_t s);
 
 // Device-wide stable LSD radix sort (descending float order) of one array.

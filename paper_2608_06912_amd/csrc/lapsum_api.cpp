@@ -115,7 +115,7 @@ int check_ws(void* ws, size_t have, size_t need) {
 // ------------------------------------------------------------- long rows --
 struct FullWs {
   void* base;       // the long rows' solve works from here
-  SortBuffers sb;   // the permutation's sort, after the solve
+  SortBuffers sb;   // the permutation's sort, before the solve
 };
 
 // Rows solved by one set of launches: as many as fit in kLongRowsBytes of
@@ -142,14 +142,15 @@ FullWs carve_full(Carve& c, int64_t batch, int64_t n, bool with_vals) {
   // (room that the size of a row's workspace has always counted)
   c.take<double>(static_cast<size_t>(tiles_of(n) < 1 ? 1 : tiles_of(n)) * kSolveTileDoubles);
   c.take<SolveRec>(1);
-  // the solve works in the same memory, before the sort
+  // the solve works in the same memory, after the sort
   const size_t need = long_solve_bytes(long_rows(batch, n), n);
   if (c.size() < need) c.take<char>(need - c.off);
   w.base = w.sb.keys[0];
   return w;
 }
 
-// Solve `batch` long rows for b and emit p.
+// Solve `batch` long rows for b and emit p (each group of rows while it is
+// still in the caches).
 int long_forward(const float* scores, int64_t batch, int64_t n, double k, double t, float* p,
                  double* b, void* ws, hipStream_t s) {
   const int64_t step = long_rows(batch, n);
@@ -704,9 +705,8 @@ int lapsum_forward(const float* scores, int64_t batch, int64_t n, double k, doub
   }
   Carve c(workspace);
   FullWs w = carve_full(c, batch, n, perm_out != nullptr);
-  const int st = long_forward(scores, batch, n, k, t, p, b, w.base, stream);
-  if (st != LAPSUM_OK || !perm_out) return st;
-  for (int64_t row = 0; row < batch; ++row) {
+  // the sort first: p may be written over the scores
+  for (int64_t row = 0; perm_out && row < batch; ++row) {
     const uint32_t* keys = nullptr;
     const int32_t* vals = nullptr;
     LAPSUM_TRY(launch_sort(scores + row * n, nullptr, nullptr, true, n, nullptr, w.sb, 0xfu, &keys,
@@ -714,15 +714,26 @@ int lapsum_forward(const float* scores, int64_t batch, int64_t n, double k, doub
     LAPSUM_TRY(hipMemcpyAsync(perm_out + row * n, vals, static_cast<size_t>(n) * sizeof(int32_t),
                               hipMemcpyDeviceToDevice, stream));
   }
-  return LAPSUM_OK;
+  return long_forward(scores, batch, n, k, t, p, b, w.base, stream);
+}
+
+// Long rows of the backward launched together (one grid.y each), with the
+// reduce partials of all of them in the workspace: at most kVjpParts blocks'
+// (4 MiB), one row always.
+constexpr int64_t kVjpParts = int64_t(1) << 17;
+
+int64_t vjp_rows(int64_t batch, int64_t n) {
+  const int64_t most = kVjpParts / vjp_reduce_blocks(n);
+  const int64_t rows = most < 65535 ? most : 65535;
+  return batch < rows ? (batch < 1 ? 1 : batch) : rows;
 }
 
 size_t lapsum_backward_workspace_size(int64_t batch, int64_t n) {
-  (void)batch;
   if (n <= kRowOnChipMax) return 0;
+  const size_t rows = static_cast<size_t>(vjp_rows(batch, n));
   Carve c(nullptr);
-  c.take<double>(4 * static_cast<size_t>(vjp_reduce_blocks(n)));
-  c.take<double>(2);
+  c.take<double>(rows * 4 * static_cast<size_t>(vjp_reduce_blocks(n)));
+  c.take<double>(rows * 2);
   return c.size();
 }
 
@@ -744,16 +755,17 @@ int lapsum_backward(const float* grad_p, const float* p, const double* b, int64_
   }
   Carve c(workspace);
   const int nb = vjp_reduce_blocks(n);
-  double* partials = c.take<double>(4 * static_cast<size_t>(nb));
-  double* coef = c.take<double>(2);
-  for (int64_t row = 0; row < batch; ++row) {
+  const int64_t step = vjp_rows(batch, n);
+  double* partials = c.take<double>(static_cast<size_t>(step) * 4 * static_cast<size_t>(nb));
+  double* coef = c.take<double>(static_cast<size_t>(step) * 2);
+  for (int64_t row = 0; row < batch; row += step) {
+    const int64_t rows = batch - row < step ? batch - row : step;
     const int64_t o = row * n;
-    LAPSUM_TRY(launch_vjp_reduce(grad_p + o, p + o, n, partials, nb, t, coef,
-                                 grad_k ? grad_k + row : nullptr,
-                                 grad_alpha ? grad_alpha + row : nullptr, stream));
-    LAPSUM_TRY(launch_vjp_emit(grad_p + o, p + o, n, coef, partials, nb, t,
-                               grad_k ? grad_k + row : nullptr,
-                               grad_alpha ? grad_alpha + row : nullptr, grad_r + o, stream));
+    double* gk = grad_k ? grad_k + row : nullptr;
+    double* ga = grad_alpha ? grad_alpha + row : nullptr;
+    LAPSUM_TRY(launch_vjp_reduce(grad_p + o, p + o, rows, n, partials, nb, t, coef, gk, ga, stream));
+    LAPSUM_TRY(launch_vjp_emit(grad_p + o, p + o, rows, n, coef, partials, nb, t, gk, ga,
+                               grad_r + o, stream));
   }
   return LAPSUM_OK;
 }

@@ -135,9 +135,10 @@ int vjp_reduce_blocks(int64_t n) {
 // through an unrolled period of three).  Loads past a wave's last tile read
 // one line of its first tile instead; only lanes that need g load it.  The
 // float4s past the whole tiles and the scalar tail go to the last workgroup.
+// One row per grid.y; 16-byte loads at any 4-byte alignment.
 template <bool PARAMS>
-__global__ __launch_bounds__(kStreamThreads, 4) void vjp_reduce_kernel(const float* __restrict__ g,
-                                                                    const float* __restrict__ p,
+__global__ __launch_bounds__(kStreamThreads, 4) void vjp_reduce_kernel(const float* __restrict__ gs,
+                                                                    const float* __restrict__ ps,
                                                                     int64_t n,
                                                                     double* __restrict__ partials) {
   constexpr int NS = PARAMS ? 4 : 2;
@@ -146,9 +147,9 @@ __global__ __launch_bounds__(kStreamThreads, 4) void vjp_reduce_kernel(const flo
   const int tid = threadIdx.x;
   const int lane = lane_id();
   const int wid = tid / kWave;
-  const bool vec = ((reinterpret_cast<uintptr_t>(g) | reinterpret_cast<uintptr_t>(p)) & 15) == 0;
-  const float4* p4 = reinterpret_cast<const float4*>(p);
-  const float4* g4 = reinterpret_cast<const float4*>(g);
+  const float* g = gs + static_cast<int64_t>(blockIdx.y) * n;
+  const float* p = ps + static_cast<int64_t>(blockIdx.y) * n;
+  partials += static_cast<int64_t>(blockIdx.y) * gridDim.x * NS;
   double F = 0.0, G = 0.0, Us = 0.0, H = 0.0;
   // one float4 of p with its g (g meaningful only where some f != 0).  No
   // contraction into fused multiply-adds, so that both instances (with and
@@ -191,20 +192,20 @@ __global__ __launch_bounds__(kStreamThreads, 4) void vjp_reduce_kernel(const flo
     }
   };
 
-  if (vec) {
+  {
     const int64_t n4 = n / 4;
     const int64_t nt = n / 1024;   // whole wave tiles
     const int64_t GW = static_cast<int64_t>(gridDim.x) * W;
     const int64_t w0 = static_cast<int64_t>(blockIdx.x) * W + wid;
     const int cnt = w0 < nt ? static_cast<int>((nt - w0 + GW - 1) / GW) : 0;
     if (cnt > 0) {
-      const float4* pd = p4 + w0 * 256;   // the line loads past the end read
+      const float* pd = p + 4 * (w0 * 256);   // the line loads past the end read
       auto base_of = [&](int j) { return (w0 + static_cast<int64_t>(j) * GW) * 256 + lane; };
       auto load_p = [&](float4 (&q)[4], int j) {
         const bool real = j < cnt;
         const int64_t b = base_of(j);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) q[u] = load_stream4(reinterpret_cast<const float*>(real ? p4 + b + 64 * u : pd));
+        for (int u = 0; u < 4; ++u) q[u] = load_stream4(real ? p + 4 * (b + 64 * u) : pd);
       };
       // tile s: its p loaded, the p of tiles s + 1 and s + 2 issued, then
       // its g (issued after them, so waiting for g waits for tile s + 1's p
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(kStreamThreads, 4) void vjp_reduce_kernel(const flo
           // only lanes that need g load it (a lane that needs none issues no
           // request); g is used within this step, so no register is copied
           gq[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-          if (need) gq[u] = g4[b + 64 * u];
+          if (need) gq[u] = load_quad(g + 4 * (b + 64 * u));
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) add4(pc[u], gq[u]);
@@ -241,15 +242,11 @@ __global__ __launch_bounds__(kStreamThreads, 4) void vjp_reduce_kernel(const flo
     if (blockIdx.x == gridDim.x - 1) {
       // the float4s past the whole tiles, then the scalars past them
       for (int64_t i = nt * 256 + tid; i < n4; i += kStreamThreads) {
-        const float4 pv = p4[i];
-        add4(pv, g4[i]);
+        const float4 pv = load_quad(p + 4 * i);
+        add4(pv, load_quad(g + 4 * i));
       }
       for (int64_t j = n4 * 4 + tid; j < n; j += kStreamThreads) add1(p[j], g[j]);
     }
-  } else {
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kStreamThreads;
-    for (int64_t j = static_cast<int64_t>(blockIdx.x) * kStreamThreads + tid; j < n; j += stride)
-      add1(p[j], g[j]);
   }
   F = wave_sum(F);
   G = wave_sum(G);
@@ -319,7 +316,7 @@ __device__ void vjp_coefs(const double (&tot)[NS], double inv_t, double* coef, d
   }
 }
 
-// One block: the coefficients of the emit from the partials of a long row.
+// One block per row: the coefficients of the emit from the partials of a long row.
 template <bool PARAMS>
 __global__ __launch_bounds__(1024) void vjp_finalize_kernel(const double* __restrict__ partials,
                                                             int nparts, double inv_t,
@@ -330,34 +327,39 @@ __global__ __launch_bounds__(1024) void vjp_finalize_kernel(const double* __rest
   constexpr int NS = PARAMS ? 4 : 2;
   __shared__ double red[NS][T / kWave];
   double tot[NS];
-  vjp_totals<NS, T>(partials, nparts, red, tot);
-  if (threadIdx.x == 0) vjp_coefs<PARAMS, NS>(tot, inv_t, coef, grad_k, grad_alpha);
+  const int64_t row = blockIdx.x;
+  vjp_totals<NS, T>(partials + row * nparts * NS, nparts, red, tot);
+  if (threadIdx.x == 0)
+    vjp_coefs<PARAMS, NS>(tot, inv_t, coef + 2 * row, grad_k ? grad_k + row : nullptr,
+                          grad_alpha ? grad_alpha + row : nullptr);
 }
 
 // Rows whose reduce leaves at most this many partials skip the finalize:
 // every emit block sums them itself (at most 4 KB each).
 constexpr int kFoldParts = 256;
 
-hipError_t launch_vjp_reduce(const float* g, const float* p, int64_t n, double* partials,
-                             int nblocks, double t, double* coef, double* grad_k,
+hipError_t launch_vjp_reduce(const float* g, const float* p, int64_t rows, int64_t n,
+                             double* partials, int nblocks, double t, double* coef, double* grad_k,
                              double* grad_alpha, hipStream_t s) {
+  if (rows < 1 || rows > 65535) return hipErrorInvalidValue;
+  const unsigned ry = static_cast<unsigned>(rows);
   const bool params = grad_k || grad_alpha;
   { ProfScope ps_("vjp_reduce", s);
   if (params)
-    hipLaunchKernelGGL(vjp_reduce_kernel<true>, dim3(nblocks), dim3(kStreamThreads), 0, s, g, p,
-                       n, partials);
+    hipLaunchKernelGGL(vjp_reduce_kernel<true>, dim3(nblocks, ry), dim3(kStreamThreads), 0, s, g,
+                       p, n, partials);
   else
-    hipLaunchKernelGGL(vjp_reduce_kernel<false>, dim3(nblocks), dim3(kStreamThreads), 0, s, g, p,
-                       n, partials); }
+    hipLaunchKernelGGL(vjp_reduce_kernel<false>, dim3(nblocks, ry), dim3(kStreamThreads), 0, s, g,
+                       p, n, partials); }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (nblocks <= kFoldParts) return hipSuccess;   // the emit combines the partials
   { ProfScope ps_("vjp_finalize", s);
   if (params)
-    hipLaunchKernelGGL(vjp_finalize_kernel<true>, dim3(1), dim3(1024), 0, s, partials, nblocks,
+    hipLaunchKernelGGL(vjp_finalize_kernel<true>, dim3(ry), dim3(1024), 0, s, partials, nblocks,
                        1.0 / t, coef, grad_k, grad_alpha);
   else
-    hipLaunchKernelGGL(vjp_finalize_kernel<false>, dim3(1), dim3(1024), 0, s, partials, nblocks,
+    hipLaunchKernelGGL(vjp_finalize_kernel<false>, dim3(ry), dim3(1024), 0, s, partials, nblocks,
                        1.0 / t, coef, grad_k, grad_alpha); }
   return hipGetLastError();
 }
@@ -371,59 +373,59 @@ constexpr int64_t kNtStoreMin = int64_t(1) << 24;
 
 // FOLD: coef comes from the reduce partials, summed by every block in the
 // same order (block 0 also stores the parameter gradients); otherwise from
-// the finalize.
+// the finalize.  One row per grid.y; 16-byte accesses at any 4-byte alignment.
 template <bool NT, bool FOLD, bool PARAMS>
-__global__ __launch_bounds__(kStreamThreads) void vjp_emit_kernel(const float* __restrict__ g,
-                                                                  const float* __restrict__ p,
+__global__ __launch_bounds__(kStreamThreads) void vjp_emit_kernel(const float* __restrict__ gs,
+                                                                  const float* __restrict__ ps,
                                                                   int64_t n,
                                                                   const double* __restrict__ coef2,
                                                                   const double* __restrict__ partials,
                                                                   int nparts, double inv_t,
                                                                   double* __restrict__ grad_k,
                                                                   double* __restrict__ grad_alpha,
-                                                                  float* __restrict__ grad) {
+                                                                  float* __restrict__ grads) {
+  const int64_t row = blockIdx.y;
+  const float* g = gs + row * n;
+  const float* p = ps + row * n;
+  float* grad = grads + row * n;
   float coef, scale;
   if constexpr (FOLD) {
     constexpr int NS = PARAMS ? 4 : 2;
     __shared__ double red[NS][kStreamThreads / kWave];
     double tot[NS];
-    vjp_totals<NS, kStreamThreads>(partials, nparts, red, tot);
+    vjp_totals<NS, kStreamThreads>(partials + row * nparts * NS, nparts, red, tot);
     double c[2];
-    vjp_coefs<PARAMS, NS>(tot, inv_t, c, blockIdx.x == 0 && threadIdx.x == 0 ? grad_k : nullptr,
-                          blockIdx.x == 0 && threadIdx.x == 0 ? grad_alpha : nullptr);
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    vjp_coefs<PARAMS, NS>(tot, inv_t, c, first && grad_k ? grad_k + row : nullptr,
+                          first && grad_alpha ? grad_alpha + row : nullptr);
     coef = static_cast<float>(c[0]);
     scale = static_cast<float>(c[1]);
   } else {
-    coef = static_cast<float>(coef2[0]);
-    scale = static_cast<float>(coef2[1]);
+    coef = static_cast<float>(coef2[2 * row]);
+    scale = static_cast<float>(coef2[2 * row + 1]);
   }
   const int tid = threadIdx.x;
   const int64_t base = static_cast<int64_t>(blockIdx.x) * kStreamTile;
-  const bool vec =
-      ((reinterpret_cast<uintptr_t>(g) | reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(grad)) & 15) == 0;
-  if (vec && base + kStreamTile <= n) {
-    const float4* p4 = reinterpret_cast<const float4*>(p + base);
-    const float4* g4 = reinterpret_cast<const float4*>(g + base);
-    float4* o4 = reinterpret_cast<float4*>(grad + base);
+  if (base + kStreamTile <= n) {
     float4 pv[kStreamVec];
 #pragma unroll
-    for (int j = 0; j < kStreamVec; ++j) pv[j] = p4[j * kStreamThreads + tid];
+    for (int j = 0; j < kStreamVec; ++j) pv[j] = load_quad(p + base + 4 * (j * kStreamThreads + tid));
 #pragma unroll
     for (int j = 0; j < kStreamVec; ++j) {
       const float fx = fminf(pv[j].x, 1.0f - pv[j].x), fy = fminf(pv[j].y, 1.0f - pv[j].y);
       const float fz = fminf(pv[j].z, 1.0f - pv[j].z), fw = fminf(pv[j].w, 1.0f - pv[j].w);
       float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
       if ((fx + fy) + (fz + fw) != 0.0f) {
-        const float4 gv = g4[j * kStreamThreads + tid];
+        const float4 gv = load_quad(g + base + 4 * (j * kStreamThreads + tid));
         o.x = fx * scale * (gv.x - coef);
         o.y = fy * scale * (gv.y - coef);
         o.z = fz * scale * (gv.z - coef);
         o.w = fw * scale * (gv.w - coef);
       }
       if constexpr (NT)
-        store_stream4(reinterpret_cast<float*>(o4 + j * kStreamThreads + tid), o);
+        store_stream4(grad + base + 4 * (j * kStreamThreads + tid), o);
       else
-        o4[j * kStreamThreads + tid] = o;
+        store_quad(grad + base + 4 * (j * kStreamThreads + tid), o);
     }
   } else {
     for (int64_t i = base + tid; i < n && i < base + kStreamTile; i += kStreamThreads) {
@@ -434,16 +436,17 @@ __global__ __launch_bounds__(kStreamThreads) void vjp_emit_kernel(const float* _
   }
 }
 
-hipError_t launch_vjp_emit(const float* g, const float* p, int64_t n, const double* coef,
+hipError_t launch_vjp_emit(const float* g, const float* p, int64_t rows, int64_t n, const double* coef,
                            const double* partials, int nparts, double t, double* grad_k,
                            double* grad_alpha, float* grad, hipStream_t s) {
   const int64_t blocks = (n + kStreamTile - 1) / kStreamTile;
-  const dim3 grid(static_cast<unsigned>(blocks)), block(kStreamThreads);
+  if (rows < 1 || rows > 65535) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(rows)), block(kStreamThreads);
   const double inv_t = 1.0 / t;
   const bool params = grad_k || grad_alpha;
   { ProfScope ps_("vjp_emit", s);
   if (nparts > kFoldParts) {
-    if (n >= kNtStoreMin)
+    if (rows * n >= kNtStoreMin)
       hipLaunchKernelGGL((vjp_emit_kernel<true, false, false>), grid, block, 0, s, g, p, n, coef,
                          partials, nparts, inv_t, grad_k, grad_alpha, grad);
     else
