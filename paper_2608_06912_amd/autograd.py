@@ -28,19 +28,23 @@ from . import (lapsum_backward, lapsum_backward_band, lapsum_bracket_noise, laps
 __all__ = ["soft_topk", "hard_topk_mask", "straight_through", "choose_path", "sample_size",
            "bracket_noise", "bracket_indices", "LapSumFunction", "FULL_SORT_MAX_N"]
 
-# Rows up to this length take the full sort; longer rows the sample bracket.
-# §4 places the switch where the two paths cost the same.  On MI355X, one
-# Gaussian row, forward + backward, sort against bracket: 0.065 / 0.072 ms
-# at n = 2^17, 0.069 / 0.072 at 2^18, 0.076 / 0.074 at 4e5 and 0.088 / 0.072
-# at 2^20 with k = n/20, alpha = -0.05; 0.069 / 0.069 at 2^18 and 0.075 /
-# 0.071 at 4e5 with k = n/16, alpha = -1; with k = 1000, alpha = -0.05 the
-# bracket is ahead from 2^17 on.  Batches of 8 rows of 2^18: 0.533 / 0.487.
-FULL_SORT_MAX_N = 1 << 18
+# A row up to this length takes the full path; longer rows the sample bracket.
+# §4 places the switch where the two paths cost the same.  On MI355X, forward
+# + backward of one Gaussian row, full against bracket: 0.12 / 0.17 ms at
+# n = 2^18 .. 2^22 (both host-bound), 0.14 / 0.19 at 2^23 and 0.23 / 0.21 at
+# 2^24 with k = n/20, alpha = -0.05; 0.15 / 0.20 at 2^24 with k = n/16,
+# alpha = -1; 0.12 / 0.17 at 2^23 with k = 1000, alpha = -0.05.  The full
+# path takes the rows of a batch together, and then waits for their bytes:
+# 8 rows, 0.11 / 0.60 at 2^20, 0.67 / 0.72 at 2^22, 1.1 / 0.87 at 6e6 with
+# k = n/20, alpha = -0.05.
+FULL_SORT_MAX_N = 1 << 23
+FULL_SORT_MAX_N_BATCH = 1 << 22
 
 
-def choose_path(n: int) -> str:
-    """"full" for n <= FULL_SORT_MAX_N, else "bracketed"."""
-    return "full" if n <= FULL_SORT_MAX_N else "bracketed"
+def choose_path(n: int, batch: int = 1) -> str:
+    """"full" for n <= FULL_SORT_MAX_N (FULL_SORT_MAX_N_BATCH for the rows of
+    a batch), else "bracketed"."""
+    return "full" if n <= (FULL_SORT_MAX_N if batch == 1 else FULL_SORT_MAX_N_BATCH) else "bracketed"
 
 
 def sample_size(n: int, rule: str = "n23") -> int:
@@ -193,7 +197,7 @@ def soft_topk(scores, k, alpha, *, path: str = "auto", sample: str = "n23", z: f
     gradient; k must then be an integer."""
     n = scores.shape[-1]
     if path == "auto":
-        path = choose_path(n)
+        path = choose_path(n, scores.numel() // n if n else 1)
     K = sample_size(n, sample) if path == "bracketed" else 0
     if not ste:
         return LapSumFunction.apply(scores, k, alpha, path, K, z, noise_seed, False, sampler)

@@ -48,7 +48,7 @@ constexpr int LW = LT / kWave;
 constexpr int kStage = 512;               // members a wave of long_pass stages
 constexpr int kLongQuads = 4;             // 16-byte loads in flight per thread
 constexpr int64_t kLongTile = static_cast<int64_t>(LT) * 4;   // scores per step of a block
-constexpr int kRootCap = 12288;           // entries long_root narrows in LDS
+constexpr int kRootCap = 24576;           // entries long_root narrows in LDS (half with weights)
 
 // A window of one row.  Cells run downwards: cell 0 above xcap (the sample's
 // largest score, or xhi), cells 1 .. NC-2 equal steps of value down to
@@ -579,7 +579,7 @@ __global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
   static_assert(NC <= WT && WT % NC == 0, "cells are spread over the threads");
   __shared__ NarrowSmem<WT> nsm;
   __shared__ float lv[kRootCap];
-  __shared__ uint32_t lw[kRootCap];
+  uint32_t* lw = reinterpret_cast<uint32_t*>(lv) + kRootCap / 2;   // with merged cells
   __shared__ double pU[GR][NC], pD[GR][NC];
   __shared__ uint32_t pc[GR][NC];
   __shared__ double U[NC], D[NC];
@@ -803,8 +803,17 @@ __global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
   }
   __syncthreads();
   const uint32_t total = pre_n[kLongMaxBlocks];
+  // the weight of an entry of block bb (a merged cell stands for its count)
+  auto weight_of = [&](int bb, float x) -> uint32_t {
+    const int c = cell_of<NC>(w, x);
+    const uint32_t* off = o.off + (s0 + bb) * (NC + 1);
+    return off[c + 1] - off[c] == 1u ? o.cnt[(s0 + bb) * NC + c] : 1u;
+  };
+  // from the middle of the cell
+  const float x0 = static_cast<float>(0.5 * (edge[js[0]] + edge[js[0] + 1]));
+  const uint32_t weight = ab[jn + 1] - ab[jp];
   double b;
-  if (direct && total <= static_cast<uint32_t>(kRootCap)) {
+  if (direct && total <= static_cast<uint32_t>(merged ? kRootCap / 2 : kRootCap)) {
 #pragma unroll 2
     for (uint32_t e = tid; e < total; e += WT) {
       int lo = 0, hi = G;   // pre_n[lo] <= e < pre_n[hi]
@@ -813,22 +822,27 @@ __global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
         if (pre_n[mid] <= e) lo = mid; else hi = mid;
       }
       const float x = o.list[at_n[lo] + (e - pre_n[lo])];
-      uint32_t wgt = 1u;
-      if (merged) {
-        const int c = cell_of<NC>(w, x);
-        const uint32_t* off = o.off + (s0 + lo) * (NC + 1);
-        if (off[c + 1] - off[c] == 1u) wgt = o.cnt[(s0 + lo) * NC + c];
-      }
       lv[e] = x;
-      lw[e] = wgt;
+      if (merged) lw[e] = weight_of(lo, x);
     }
     // (each thread reads back only what it wrote)
     auto each = [&](auto&& f) {
-      for (uint32_t e = tid; e < total; e += WT) f(lv[e], lw[e]);
+      for (uint32_t e = tid; e < total; e += WT) f(lv[e], merged ? lw[e] : 1u);
     };
-    // from the middle of the cell
-    const float x0 = static_cast<float>(0.5 * (edge[js[0]] + edge[js[0] + 1]));
-    b = narrow_solve<WT>(each, total, ab[jn + 1] - ab[jp], ext, -INFINITY, INFINITY, x0, k, t, nsm);
+    b = narrow_solve<WT>(each, total, weight, ext, -INFINITY, INFINITY, x0, k, t, nsm);
+  } else if (direct) {
+    // more entries than LDS holds: straight from the blocks' lists, a wave
+    // per block
+    auto each = [&](auto&& f) {
+      for (int bb = wid; bb < G; bb += W) {
+        const uint32_t cnt = pre_n[bb + 1] - pre_n[bb];
+        for (uint32_t e = lane; e < cnt; e += kWave) {
+          const float x = o.list[at_n[bb] + e];
+          f(x, merged ? weight_of(bb, x) : 1u);
+        }
+      }
+    };
+    b = narrow_solve<WT>(each, total, weight, ext, -INFINITY, INFINITY, x0, k, t, nsm);
   } else {
     auto each = [&](auto&& f) {
       int64_t i = tid;
@@ -850,6 +864,7 @@ __global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
 
 // --------------------------------------------------------------- launches --
 namespace {
+// Rows past 2^24 scores take four times the sample, which halves the window.
 // Rows past 2^22 scores take 256 cells (a window can hold several percent of
 // the row, and long_root takes three cells of it), up to 512 blocks and the
 // separate merge; shorter rows 64 cells, up to 256 blocks, and merge them in
@@ -918,7 +933,9 @@ hipError_t launch_long_solve(const float* scores, int64_t rows, int64_t n, doubl
   const unsigned ry = static_cast<unsigned>(rows);
   const bool wide = long_wide(n);
   { ProfScope ps_("long_window", s);
-  if (wide)
+  if (n > (int64_t(1) << 24))
+    hipLaunchKernelGGL((long_window_kernel<64, 256>), dim3(1, ry), dim3(WT), 0, s, scores, n, k, t, o.win);
+  else if (wide)
     hipLaunchKernelGGL((long_window_kernel<16, 256>), dim3(1, ry), dim3(WT), 0, s, scores, n, k, t, o.win);
   else
     hipLaunchKernelGGL((long_window_kernel<16, 64>), dim3(1, ry), dim3(WT), 0, s, scores, n, k, t, o.win); }

@@ -63,6 +63,18 @@ def test_long_row_of_many_cells(lib, n, frac):
         _check(r, frac * n, -0.5, _np(p), float(_np(b)[0]), (n, dist, frac))
 
 
+def test_long_row_past_the_entries_kept_on_chip(lib):
+    """One cell around the root holds most of a long row's members, more than
+    LDS keeps: scores bunched within the width of a cell."""
+    n = 3_000_001
+    rng = np.random.default_rng(5)
+    r = rng.standard_normal(n).astype(np.float32)
+    r[::3] = (1.5 + 1e-6 * rng.standard_normal(r[::3].size)).astype(np.float32)
+    for k in (0.2 * n, 0.35 * n):
+        p, b = lib.lapsum_forward(_t(r), k, -0.5)
+        _check(r, k, -0.5, _np(p), float(_np(b)[0]), k)
+
+
 @pytest.mark.parametrize("batch,n", [(3, 32771), (70, 32769), (5, 400001)])
 def test_long_rows_of_a_batch(lib, batch, n):
     rng = np.random.default_rng([batch, n])
