@@ -81,7 +81,8 @@ const char* lapsum_status_string(int status);
  *            ordered by the order-preserving uint32 key of the float (so
  *            +0.0 precedes -0.0) and then by ascending original index.
  *            Asking for it makes the sort carry indices (slower).
- * Rows with n <= 32768 are solved by one workgroup per row entirely on chip,
+ * Rows with n <= 32768 are solved by one workgroup (short rows by one wave)
+ * per row entirely on chip,
  * except a batch of one row longer than 16384.  That row and all longer ones
  * are solved device-wide, several rows at a time, without sorting: a sample
  * gives a window that holds b, one pass sums the scores outside it and keeps

@@ -140,6 +140,10 @@ hipError_t launch_row_forward(const float* scores, int64_t batch, int64_t n, dou
 // b = NaN and no p (the gated launch_row_forward completes it).
 hipError_t launch_row_bucket_forward(const float* scores, int64_t batch, int64_t n, double k,
                                      double t, float* p, double* b, hipStream_t s);
+// The same for short rows, one wave per row (short_rows.hip); solves every row.
+constexpr int64_t kRowWaveMax = 1024;
+hipError_t launch_row_wave_forward(const float* scores, int64_t batch, int64_t n, double k, double t,
+                                   float* p, double* b, hipStream_t s);
 // Backward for rows with n <= kRowOnChipMax; grad_k / grad_alpha ([batch]
 // float64, each may be null) receive the budget and temperature gradients.
 hipError_t launch_row_backward(const float* grad_p, const float* p, int64_t batch, int64_t n,

@@ -671,6 +671,16 @@ bool forward_on_chip(int64_t batch, int64_t n) {
   return n <= kRowOnChipMax && !(batch == 1 && n > kRowSingleMax);
 }
 
+// Short rows take a wave each where that is faster than a workgroup each:
+// always up to 256 scores (one row 8 against 11 us, 4096 rows of 256 19.5
+// against 161), and up to kRowWaveMax from 512 rows on, when the workgroups
+// no longer run all at once (256 rows: 512 scores 15-21 against 12 us, 1024
+// scores 19-32 against 12; 1024 rows of 1024: 26-32 against 44, 2048 of 512:
+// 19-24 against 83).
+bool row_per_wave(int64_t batch, int64_t n) {
+  return n <= 256 || (n <= kRowWaveMax && batch >= 512);
+}
+
 size_t lapsum_forward_workspace_size(int64_t batch, int64_t n, int with_perm) {
   if (n < 1) return 0;
   if (forward_on_chip(batch, n)) return 0;
@@ -692,6 +702,8 @@ int lapsum_forward(const float* scores, int64_t batch, int64_t n, double k, doub
   if (forward_on_chip(batch, n)) {
     if (perm_out) {
       LAPSUM_TRY(launch_row_forward(scores, batch, n, k, t, p, b, perm_out, false, stream));
+    } else if (row_per_wave(batch, n)) {
+      LAPSUM_TRY(launch_row_wave_forward(scores, batch, n, k, t, p, b, stream));
     } else {
       // no order wanted: the bucketed solve, then the full sort only for
       // rows it left unsolved.  It leaves a row only when the root's bucket

@@ -60,6 +60,14 @@ __device__ __forceinline__ float key_mid(float lo, float hi) {
   return key_float(kh + (kl - kh) / 2u);
 }
 
+// The next point when a Newton step leaves (lo, hi): the arithmetic middle,
+// and after twenty points (or with an end still open) the middle of the
+// keys, which reaches every gap within 32 more.
+__device__ __forceinline__ float middle(float lo, float hi, int it) {
+  const float m = 0.5f * lo + 0.5f * hi;
+  return it < 20 && m > lo && m < hi ? m : key_mid(lo, hi);
+}
+
 // Each(f) calls f(value, weight) for every score of this thread's share of
 // the set, held by the BLOCK threads of the workgroup still running (higher
 // waves may have ended); `total` is the number of scores (weighted entries)
@@ -131,16 +139,15 @@ __device__ double narrow_solve(Each&& each, uint32_t total, uint32_t weight, con
     same = side == last ? same + 1 : 0;
     last = side;
     // the next point: a Newton step, longer each time the root stayed on the
-    // same side so that both ends close in; the middle of the keys between
-    // the ends when that leaves them, and after a dozen points always
-    // (at most 32 of those)
+    // same side so that both ends close in; a middle of the ends when that
+    // leaves them, and after a dozen points always
     float xn = x;
     const double F = 0.5 * (P + E);
     if (it < 12 && F > 0.0) {
       const double step = t * (f - k) / F * static_cast<double>(1 << (same < 6 ? same : 6));
       xn = static_cast<float>(xd + step);
     }
-    if (!(xn > lo && xn < hi)) xn = key_mid(lo, hi);
+    if (!(xn > lo && xn < hi)) xn = middle(lo, hi, it);
     x = xn;
     if (!(x > lo && x < hi)) break;   // no float between the ends
   }
