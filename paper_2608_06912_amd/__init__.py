@@ -30,7 +30,8 @@ __all__ = [
     "lapsum_dftopk_forward", "lapsum_dftopk_backward",
 ]
 
-LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "liblapsum.so")
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB_PATH = os.path.join(HERE, "liblapsum.so")
 LAPSUM_FLAG_FULL_SORT = 1
 NOALLOC_SCRATCH_BYTES = 64 * 1024 * 1024   # LAPSUM_NOALLOC_SCRATCH_BYTES
 

@@ -6,7 +6,8 @@ Every HIP source is compiled for gfx950 only, with packed-FP32 instructions
 disabled (-target-feature -packed-fp32-ops); the host orchestration is
 compiled without floating-point contraction so that the bracket ranks are
 evaluated exactly as written.  Objects go to _build/ next to this file and
-the library to liblapsum.so beside it.
+the library to liblapsum.so beside it; the native autograd node (a torch
+extension over liblapsum.so) to _node.so.
 """
 from __future__ import annotations
 
@@ -20,6 +21,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblapsum.so")
+NODE = os.path.join(HERE, "_node.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 
 HIP_SOURCES = ["row_kernels.hip", "stream_kernels.hip", "sort_kernels.hip",
@@ -27,6 +29,7 @@ HIP_SOURCES = ["row_kernels.hip", "stream_kernels.hip", "sort_kernels.hip",
                "comparator_kernels.hip", "noalloc.hip",
                "long_solve.hip", "short_rows.hip"]
 HOST_SOURCES = ["lapsum_api.cpp"]
+NODE_SOURCE = "autograd_node.cpp"
 
 ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"-I{INCLUDE}", f"-I{CSRC}"]
@@ -50,6 +53,19 @@ def _compile(args):
     return src
 
 
+def _node_compile(hipcc: str, rocm_inc: str, obj: str) -> list:
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    incs = [f"-I{p}" for p in include_paths()] + [f"-I{rocm_inc}",
+                                                  f"-I{sysconfig.get_paths()['include']}"]
+    return [hipcc, "-O2", "-std=c++17", "-fPIC", "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            "-DTORCH_EXTENSION_NAME=_node", "-DTORCH_API_INCLUDE_EXTENSION_H",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", *incs, "-c",
+            os.path.join(CSRC, NODE_SOURCE), "-o", obj]
+
+
 def build(verbose: bool = False, jobs: int | None = None) -> str:
     """Compile every source and link liblapsum.so; returns the library path."""
     hipcc = _hipcc()
@@ -66,19 +82,32 @@ def build(verbose: bool = False, jobs: int | None = None) -> str:
         objs.append(obj)
         work.append(([hipcc, *COMMON, *HOST_FLAGS, f"-I{rocm_inc}", "-c", os.path.join(CSRC, src),
                       "-o", obj], src))
+    node_obj = os.path.join(BUILD, NODE_SOURCE + ".o")
+    work.insert(0, (_node_compile(hipcc, rocm_inc, node_obj), NODE_SOURCE))
     jobs = jobs or min(len(work), max(1, min(8, os.cpu_count() or 1)))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
         for src in ex.map(_compile, work):
             if verbose:
                 print(f"compiled {src}", flush=True)
     tmp = LIB + ".tmp"
-    link = [hipcc, "-shared", f"--offload-arch={ARCH}", "-o", tmp, *objs]
+    link = [hipcc, "-shared", f"--offload-arch={ARCH}", "-Wl,-soname,liblapsum.so", "-o", tmp, *objs]
     proc = subprocess.run(link, capture_output=True, text=True)
     if proc.returncode != 0:
         raise RuntimeError(f"linking failed:\n{' '.join(link)}\n{proc.stderr}")
     os.replace(tmp, LIB)
     if verbose:
         print(f"built {LIB}", flush=True)
+    import torch
+    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = NODE + ".tmp"
+    link = [hipcc, "-shared", "-o", tmp, node_obj, LIB, f"-L{tlib}", "-lc10", "-lc10_hip",
+            "-ltorch_cpu", "-ltorch_python", "-ltorch", "-Wl,-rpath,$ORIGIN"]
+    proc = subprocess.run(link, capture_output=True, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError(f"linking failed:\n{' '.join(link)}\n{proc.stderr}")
+    os.replace(tmp, NODE)
+    if verbose:
+        print(f"built {NODE}", flush=True)
     return LIB
 
 

@@ -1,0 +1,82 @@
+"""The native node of the full path against LapSumFunction, the same node in
+Python: equal outputs and gradients bit for bit over the forms the entry point
+takes, and the Python node where a transform has to see it."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _both(x, k, alpha, g):
+    import torch
+
+    import paper_2608_06912_amd.autograd as A
+    n = x.shape[-1]
+    wrt = [t for t in (x, k, alpha) if isinstance(t, torch.Tensor) and t.requires_grad]
+    out = []
+    for p in (A.soft_topk(x, k, alpha, path="full"),
+              A.LapSumFunction.apply(x, k, alpha, "full", 0, 5.16, 0, False)):
+        assert p.shape == x.shape and p.dtype == torch.float32 and n > 0
+        out.append((p.detach(), *torch.autograd.grad(p, wrt, g)))
+    return out
+
+
+@pytest.mark.parametrize("shape", [(300,), (5, 40001), (2, 3, 777), (1, 4096)])
+@pytest.mark.parametrize("dtype", ["float32", "bfloat16", "float64"])
+@pytest.mark.parametrize("strided", [False, True])
+def test_native_node_equals_python_node(lib, shape, dtype, strided):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    wide = shape[:-1] + (2 * shape[-1],) if strided else shape
+    base = torch.randn(wide, generator=gen, device="cuda").to(getattr(torch, dtype))
+    x = (base[..., ::2] if strided else base).detach().requires_grad_()
+    g = torch.randn(shape, generator=gen, device="cuda")
+    k = torch.tensor(shape[-1] / 10.0, dtype=torch.float64, requires_grad=True)
+    a = torch.tensor([-0.5], device="cuda", requires_grad=True)
+    for kk, aa in ((shape[-1] / 10.0, -0.5), (k, -0.5), (shape[-1] / 10.0, a), (k, a),
+                   (k.detach(), a)):
+        native, python = _both(x, kk, aa, g)
+        assert len(native) == len(python)
+        for u, v in zip(native, python):
+            assert u.dtype == v.dtype and u.shape == v.shape and u.device == v.device
+            assert torch.equal(u, v)
+
+
+def test_native_node_expanded_gradient_and_retained_graph(lib):
+    import torch
+
+    import paper_2608_06912_amd.autograd as A
+    x = torch.randn(4, 1000, device="cuda", requires_grad=True)
+    p = A.soft_topk(x, 10.0, -1.0)
+    p.sum().backward(retain_graph=True)   # an expanded upstream gradient
+    first = x.grad.clone()
+    p.sum().backward()
+    assert torch.equal(x.grad, 2 * first)
+    # no score needs a gradient: no graph
+    assert not A.soft_topk(x.detach(), 10.0, -1.0).requires_grad
+    # the saved p is versioned
+    p = A.soft_topk(x, 10.0, -1.0)
+    with torch.no_grad():
+        p.add_(1.0)
+    with pytest.raises(RuntimeError):
+        p.sum().backward()
+
+
+def test_native_node_leaves_transforms_and_errors_to_the_python_node(lib):
+    import torch
+
+    import paper_2608_06912_amd.autograd as A
+    x = torch.randn(4, 100, device="cuda")
+    with torch.autograd.forward_ad.dual_level():
+        assert A._native_full(x, 10.0, -1.0) is None
+    seen = []
+    torch.func.vmap(lambda r: seen.append(A._native_full(r, 10.0, -1.0)) or r)(x)
+    assert seen == [None]
+    assert A._native_full(x.cpu(), 10.0, -1.0) is None
+    for k, alpha in ((0.0, -1.0), (100.0, -1.0), (10.0, 1.0)):
+        with pytest.raises(lib.LapsumError) as e:
+            A.soft_topk(x, k, alpha)
+        assert e.value.status == 1
+    packed = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: packed.append(t.shape) or t, lambda t: t):
+        A.soft_topk(x.requires_grad_(), 10.0, -1.0).sum().backward()
+    assert torch.Size([4, 100]) in packed
