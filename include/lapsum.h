@@ -176,6 +176,22 @@ int lapsum_topk_mask(const int32_t* perm, int64_t batch, int64_t n, int64_t k,
                      float* mask, hipStream_t stream);
 
 /* ------------------------------------------------------------------------
+ * The same mask straight from the scores, without the order: the k-th largest
+ * score of each row is found as the threshold of a vanishing temperature, and
+ * equal scores are taken by index (+0.0 before -0.0, as in perm_out).
+ *
+ *   scores     [batch, n] float32 input, not overlapping mask
+ *   k          integer count of ones per row, 0 <= k <= n
+ *   mask       [batch, n] float32 output
+ *   workspace  lapsum_hard_mask_workspace_size(batch, n) bytes, 256-aligned
+ * ------------------------------------------------------------------------ */
+size_t lapsum_hard_mask_workspace_size(int64_t batch, int64_t n);
+
+int lapsum_hard_mask(const float* scores, int64_t batch, int64_t n, int64_t k,
+                     float* mask, void* workspace, size_t workspace_bytes,
+                     hipStream_t stream);
+
+/* ------------------------------------------------------------------------
  * Comparators (not part of the operator): the two methods the paper measures
  * Fast LapSum against, so that its speed and budget claims can be checked on
  * this device.

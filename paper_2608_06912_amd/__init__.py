@@ -26,7 +26,8 @@ __all__ = [
     "lapsum_forward_bracketed_workspace_size", "lapsum_forward_bracketed", "lapsum_bracket_noise",
     "LAPSUM_FLAG_FULL_SORT", "LIB_PATH", "lapsum_profile_start", "lapsum_profile_stop",
     "lapsum_band_size", "new_band", "lapsum_backward_band_workspace_size", "lapsum_backward_band",
-    "lapsum_topk_mask", "lapsum_bisect_forward", "lapsum_dftopk_workspace_size",
+    "lapsum_topk_mask", "lapsum_hard_mask", "lapsum_hard_mask_workspace_size",
+    "lapsum_bisect_forward", "lapsum_dftopk_workspace_size",
     "lapsum_dftopk_forward", "lapsum_dftopk_backward",
 ]
 
@@ -111,6 +112,10 @@ def load():
     lib.lapsum_dftopk_backward.restype = i32
     lib.lapsum_topk_mask.argtypes = [vp, i64, i64, i64, vp, vp]
     lib.lapsum_topk_mask.restype = i32
+    lib.lapsum_hard_mask_workspace_size.argtypes = [i64, i64]
+    lib.lapsum_hard_mask_workspace_size.restype = sz
+    lib.lapsum_hard_mask.argtypes = [vp, i64, i64, i64, vp, vp, sz, vp]
+    lib.lapsum_hard_mask.restype = i32
     lib.lapsum_profile_start.argtypes = []
     lib.lapsum_profile_start.restype = i32
     lib.lapsum_profile_stop.argtypes = []
@@ -309,6 +314,27 @@ def lapsum_topk_mask(perm, k: int, *, out=None):
     with _on_device(dev):
         _check(lib.lapsum_topk_mask(_ptr(perm), int(batch), int(n), int(k), _ptr(mask),
                                     _stream(dev)), "lapsum_topk_mask")
+    return mask
+
+
+def lapsum_hard_mask_workspace_size(batch: int, n: int) -> int:
+    return int(load().lapsum_hard_mask_workspace_size(batch, n))
+
+
+def lapsum_hard_mask(scores, k: int, *, workspace=None):
+    """The hard top-k mask straight from the scores (no order formed): 1.0 for
+    the k largest of each row, equal scores by index, 0.0 elsewhere."""
+    torch = _torch()
+    lib = load()
+    batch, n = _rows(scores, "scores")
+    if int(k) != k:
+        raise ValueError("k must be an integer count")
+    dev = scores.device
+    mask = torch.empty_like(scores)
+    ws, nbytes = _workspace(lib.lapsum_hard_mask_workspace_size(batch, n), dev, workspace)
+    with _on_device(dev):
+        _check(lib.lapsum_hard_mask(_ptr(scores), batch, n, int(k), _ptr(mask), _ptr(ws), nbytes,
+                                    _stream(dev)), "lapsum_hard_mask")
     return mask
 
 

@@ -28,7 +28,7 @@ import os
 import torch
 
 from . import (HERE, LapsumError, lapsum_backward, lapsum_backward_band, lapsum_bracket_noise,
-               lapsum_forward, lapsum_forward_bracketed, lapsum_topk_mask, load, new_band)
+               lapsum_forward, lapsum_forward_bracketed, lapsum_hard_mask, load, new_band)
 
 __all__ = ["soft_topk", "hard_topk_mask", "straight_through", "choose_path", "sample_size",
            "bracket_noise", "bracket_indices", "LapSumFunction", "FULL_SORT_MAX_N"]
@@ -196,8 +196,8 @@ def _load_node():
 _PLAIN = (torch.Tensor, torch.nn.Parameter)
 
 
-def _native_full(scores, k, alpha):
-    """p of the full path through the native node, or None where the Python
+def _native_full(scores, k, alpha, ste=False):
+    """p of the full path (ste: the hard mask with p's gradient) through the native node, or None where the Python
     node has to run: a tensor subclass, torch function or dispatch modes,
     functorch transforms, forward-mode AD, tracing and compilation (all of
     which look at LapSumFunction), and arguments it would reject."""
@@ -216,7 +216,7 @@ def _native_full(scores, k, alpha):
     af = float(alpha.item() if at else alpha)
     node = _node or _load_node()
     try:
-        return node.full(scores, k if kt else None, alpha if at else None, kf, af)
+        return node.full(scores, k if kt else None, alpha if at else None, kf, af, ste)
     except RuntimeError:
         status = node.last_status()
         if status:
@@ -236,9 +236,7 @@ def hard_topk_mask(scores, k: int):
     x, n = _as_rows(scores)
     if int(k) != k or not 0 <= int(k) <= n:
         raise ValueError("k must be an integer in [0, n]")
-    # the descending order does not depend on the budget; n/2 is a valid one
-    _, _, perm = lapsum_forward(x, n / 2.0, -1.0, perm=True)
-    return lapsum_topk_mask(perm, int(k)).reshape(scores.shape)
+    return lapsum_hard_mask(x, int(k)).reshape(scores.shape)
 
 
 def soft_topk(scores, k, alpha, *, path: str = "auto", sample: str = "n23", z: float = 5.16,
@@ -253,20 +251,12 @@ def soft_topk(scores, k, alpha, *, path: str = "auto", sample: str = "n23", z: f
     n = scores.shape[-1]
     if path == "auto":
         path = choose_path(n, scores.numel() // n if n else 1)
-    if path == "full" and not ste:
-        p = _native_full(scores, k, alpha)
-        if p is not None:
-            return p
-    K = sample_size(n, sample) if path == "bracketed" else 0
-    if not ste:
-        return LapSumFunction.apply(scores, k, alpha, path, K, z, noise_seed, False, sampler)
-    kf = float(k)
-    if int(kf) != kf:
+    if ste and int(float(k)) != float(k):
         raise ValueError("ste=True needs an integer k")
     if path == "full":
-        p, perm = LapSumFunction.apply(scores, k, alpha, path, K, z, noise_seed, True, sampler)
-        m = lapsum_topk_mask(perm.reshape(-1, n).contiguous(), int(kf)).reshape(scores.shape)
-    else:
-        p = LapSumFunction.apply(scores, k, alpha, path, K, z, noise_seed, False, sampler)
-        m = hard_topk_mask(scores.detach(), int(kf))
-    return straight_through(p, m)
+        out = _native_full(scores, k, alpha, ste)
+        if out is not None:
+            return out
+    K = sample_size(n, sample) if path == "bracketed" else 0
+    p = LapSumFunction.apply(scores, k, alpha, path, K, z, noise_seed, False, sampler)
+    return straight_through(p, hard_topk_mask(scores.detach(), int(float(k)))) if ste else p

@@ -27,7 +27,7 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 HIP_SOURCES = ["row_kernels.hip", "stream_kernels.hip", "sort_kernels.hip",
                "solve_kernels.hip", "bracket_kernels.hip", "band_kernels.hip", "bucket_solve.hip",
                "comparator_kernels.hip", "noalloc.hip",
-               "long_solve.hip", "short_rows.hip"]
+               "long_solve.hip", "short_rows.hip", "hard_mask.hip"]
 HOST_SOURCES = ["lapsum_api.cpp"]
 NODE_SOURCE = "autograd_node.cpp"
 

@@ -46,7 +46,7 @@ void* ptr(const Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; }
 struct FullNode : public torch::autograd::Function<FullNode> {
   static Tensor forward(AutogradContext* ctx, const Tensor& scores,
                         const std::optional<Tensor>& k_like,
-                        const std::optional<Tensor>& alpha_like, double k, double alpha) {
+                        const std::optional<Tensor>& alpha_like, double k, double alpha, bool ste) {
     const c10::DeviceGuard guard(scores.device());
     Tensor x = scores.detach();
     if (x.scalar_type() != at::kFloat) x = x.to(at::kFloat);
@@ -60,18 +60,29 @@ struct FullNode : public torch::autograd::Function<FullNode> {
     check(lapsum_forward(x.data_ptr<float>(), batch, n, k, alpha, p.data_ptr<float>(),
                          b.data_ptr<double>(), nullptr, ptr(ws), need, stream_of(x)),
           "lapsum_forward");
+    // straight-through: the mask goes forward (p + (m - p) is m exactly in
+    // float32), p's gradient backward
+    Tensor out = p;
+    if (ste) {
+      out = at::empty(x.sizes(), x.options());
+      const size_t mneed = lapsum_hard_mask_workspace_size(batch, n);
+      Tensor mws = bytes(mneed, x);
+      check(lapsum_hard_mask(x.data_ptr<float>(), batch, n, static_cast<int64_t>(k),
+                             out.data_ptr<float>(), ptr(mws), mneed, stream_of(x)),
+            "lapsum_hard_mask");
+    }
     ctx->save_for_backward({p});
     ctx->saved_data["alpha"] = alpha;
     // (for their shape, dtype and device)
     if (k_like) ctx->saved_data["k_like"] = *k_like;
     if (alpha_like) ctx->saved_data["alpha_like"] = *alpha_like;
-    return p;
+    return out;
   }
 
   static variable_list backward(AutogradContext* ctx, variable_list grads) {
     const Tensor p = ctx->get_saved_variables()[0].detach();
     Tensor g = grads[0];
-    if (!g.defined()) return {Tensor(), Tensor(), Tensor(), Tensor(), Tensor()};
+    if (!g.defined()) return variable_list(6);
     const c10::DeviceGuard guard(p.device());
     const at::AutoDispatchBelowADInplaceOrView below;
     if (g.scalar_type() != at::kFloat) g = g.to(at::kFloat);
@@ -114,7 +125,7 @@ struct FullNode : public torch::autograd::Function<FullNode> {
       if (want_a) grad_a = pick(1, al);
     }
     if (!ctx->needs_input_grad(0)) grad = Tensor();
-    return {grad, grad_k, grad_a, Tensor(), Tensor()};
+    return {grad, grad_k, grad_a, Tensor(), Tensor(), Tensor()};
   }
 };
 
@@ -122,8 +133,8 @@ struct FullNode : public torch::autograd::Function<FullNode> {
 
 PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
   m.def("full", [](const Tensor& scores, const std::optional<Tensor>& k_like,
-                   const std::optional<Tensor>& alpha_like, double k, double alpha) {
-    return FullNode::apply(scores, k_like, alpha_like, k, alpha);
+                   const std::optional<Tensor>& alpha_like, double k, double alpha, bool ste) {
+    return FullNode::apply(scores, k_like, alpha_like, k, alpha, ste);
   });
   m.def("last_status", [] { return t_status; });
 }

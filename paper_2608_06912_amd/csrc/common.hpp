@@ -471,7 +471,15 @@ __device__ inline double gap_root(double k, double t, double c_up, bool has_up, 
     lny = 0.5 * (lnA - lnE);
   } else {
     const double D = sqrt(c * c + exp(lnA + lnE));   // A E <= n^2, never overflows
-    lny = (c > 0.0) ? log(c + D) - lnE : lnA - log(D - c);
+    if (c > 0.0) {
+      // (b - v)/t without the width of the gap, which would cancel: near v
+      // the root keeps v's own precision however far u is
+      const double w = lnB - log(c + D);
+      if (w < 0.5 * g) return v + t * fmax(w, 0.0);
+      lny = g - w;
+    } else {
+      lny = lnA - log(D - c);
+    }
   }
   lny = fmin(fmax(lny, 0.0), g);
   return u - t * lny;

@@ -681,6 +681,23 @@ bool row_per_wave(int64_t batch, int64_t n) {
   return n <= 256 || (n <= kRowWaveMax && batch >= 512);
 }
 
+// Rows on chip, no order wanted.
+static int rows_on_chip(const float* scores, int64_t batch, int64_t n, double k, double t, float* p,
+                        double* b, hipStream_t stream) {
+  if (row_per_wave(batch, n)) {
+    LAPSUM_TRY(launch_row_wave_forward(scores, batch, n, k, t, p, b, stream));
+    return LAPSUM_OK;
+  }
+  // the bucketed solve, then the full sort only for rows it left unsolved.
+  // It leaves a row only when the root's bucket holds more than
+  // kBucketSortCap scores, which a shorter row cannot have, so short rows
+  // need no second launch.
+  LAPSUM_TRY(launch_row_bucket_forward(scores, batch, n, k, t, p, b, stream));
+  if (n > kBucketSortCap)
+    LAPSUM_TRY(launch_row_forward(scores, batch, n, k, t, p, b, nullptr, true, stream));
+  return LAPSUM_OK;
+}
+
 size_t lapsum_forward_workspace_size(int64_t batch, int64_t n, int with_perm) {
   if (n < 1) return 0;
   if (forward_on_chip(batch, n)) return 0;
@@ -700,19 +717,8 @@ int lapsum_forward(const float* scores, int64_t batch, int64_t n, double k, doub
   if (dst != LAPSUM_OK) return dst;
   const double t = -alpha;
   if (forward_on_chip(batch, n)) {
-    if (perm_out) {
-      LAPSUM_TRY(launch_row_forward(scores, batch, n, k, t, p, b, perm_out, false, stream));
-    } else if (row_per_wave(batch, n)) {
-      LAPSUM_TRY(launch_row_wave_forward(scores, batch, n, k, t, p, b, stream));
-    } else {
-      // no order wanted: the bucketed solve, then the full sort only for
-      // rows it left unsolved.  It leaves a row only when the root's bucket
-      // holds more than kBucketSortCap scores, which a shorter row cannot
-      // have, so short rows need no second launch.
-      LAPSUM_TRY(launch_row_bucket_forward(scores, batch, n, k, t, p, b, stream));
-      if (n > kBucketSortCap)
-        LAPSUM_TRY(launch_row_forward(scores, batch, n, k, t, p, b, nullptr, true, stream));
-    }
+    if (!perm_out) return rows_on_chip(scores, batch, n, k, t, p, b, stream);
+    LAPSUM_TRY(launch_row_forward(scores, batch, n, k, t, p, b, perm_out, false, stream));
     return LAPSUM_OK;
   }
   Carve c(workspace);
@@ -789,6 +795,59 @@ int lapsum_topk_mask(const int32_t* perm, int64_t batch, int64_t n, int64_t k, f
   const int dst = check_device();
   if (dst != LAPSUM_OK) return dst;
   LAPSUM_TRY(launch_topk_mask(perm, batch, n, k, mask, stream));
+  return LAPSUM_OK;
+}
+
+// A temperature under which no two distinct float32 scores share a term and
+// every shift of the root vanishes in float32 (t ln n < 1e-57).
+constexpr double kHardT = 1e-60;
+
+size_t lapsum_hard_mask_workspace_size(int64_t batch, int64_t n) {
+  if (batch < 1 || n < 1 || n > 2147483647LL) return 0;
+  const int64_t rows = batch < 65535 ? batch : 65535;
+  Carve c(nullptr);
+  c.take<double>(static_cast<size_t>(rows));
+  c.take<char>(hard_mask_bytes(rows, n));
+  if (!forward_on_chip(batch, n)) c.take<char>(long_solve_bytes(long_rows(batch, n), n));
+  return c.size();
+}
+
+int lapsum_hard_mask(const float* scores, int64_t batch, int64_t n, int64_t k, float* mask,
+                     void* workspace, size_t workspace_bytes, hipStream_t stream) {
+  if (!scores || !mask || scores == mask || batch < 1 || n < 1 || n > 2147483647LL || k < 0 || k > n)
+    return LAPSUM_ERR_INVALID_ARG;
+  const int wst = check_ws(workspace, workspace_bytes, lapsum_hard_mask_workspace_size(batch, n));
+  if (wst != LAPSUM_OK) return wst;
+  const int dst = check_device();
+  if (dst != LAPSUM_OK) return dst;
+  if (k == 0 || k == n) {
+    LAPSUM_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(mask), batch * n,
+                               k == 0 ? 0u : 0x3f800000u, stream));
+    return LAPSUM_OK;
+  }
+  const bool on_chip = forward_on_chip(batch, n);
+  const int64_t step = batch < 65535 ? batch : 65535;
+  Carve c(workspace);
+  double* b = c.take<double>(static_cast<size_t>(step));
+  char* counts = c.take<char>(hard_mask_bytes(step, n));
+  void* ws = on_chip ? nullptr : c.take<char>(long_solve_bytes(long_rows(batch, n), n));
+  const double kh = static_cast<double>(k) - 0.5;
+  for (int64_t row = 0; row < batch; row += step) {
+    const int64_t rows = batch - row < step ? batch - row : step;
+    const float* r = scores + row * n;
+    float* m = mask + row * n;
+    if (on_chip) {
+      // (the on-chip solves also write p, which the mask then replaces)
+      const int st = rows_on_chip(r, rows, n, kh, kHardT, m, b, stream);
+      if (st != LAPSUM_OK) return st;
+    } else {
+      const int64_t ls = long_rows(batch, n);
+      for (int64_t q = 0; q < rows; q += ls)
+        LAPSUM_TRY(launch_long_solve(r + q * n, rows - q < ls ? rows - q : ls, n, kh, kHardT, ws,
+                                     b + q, stream));
+    }
+    LAPSUM_TRY(launch_hard_mask(r, rows, n, k, b, counts, m, stream));
+  }
   return LAPSUM_OK;
 }
 

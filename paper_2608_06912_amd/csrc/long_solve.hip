@@ -291,7 +291,7 @@ __global__ __launch_bounds__(LT) void long_pass_kernel(const float* __restrict__
   }
   for (int e = tid; e <= NC; e += LT) edge[e] = edge_of<NC>(w, e);
   const double xhi = w.xhi, xlo = w.xlo;
-  const float farf = static_cast<float>(fmin(150.0 / c2, 3.0e38));   // beyond: 2^-150, no part of the sums
+  const float farf = static_cast<float>(fmin(fmax(150.0 / c2, 1e-37), 3.0e38));   // beyond: 2^-150, no part of the sums
   double TR = 0.0, TL = 0.0;
   uint32_t nR = 0u;
   int staged = 0;   // members this wave has met (wave-uniform)
@@ -301,7 +301,6 @@ __global__ __launch_bounds__(LT) void long_pass_kernel(const float* __restrict__
   auto take4 = [&](const float (&v)[4]) {
     bool up[4], dn[4], in[4];
     float dmin = INFINITY;
-    bool any_in = false;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       up[e] = v[e] >= w.xhi;
@@ -309,7 +308,6 @@ __global__ __launch_bounds__(LT) void long_pass_kernel(const float* __restrict__
       in[e] = (v[e] < w.xhi) & (v[e] >= w.xlo);
       const float d = fmaxf(v[e] - w.xhi, w.xlo - v[e]);
       dmin = fminf(dmin, in[e] ? INFINITY : d);
-      any_in = any_in | in[e];
       nR += up[e] ? 1u : 0u;
     }
     if (__any(dmin < farf)) {
@@ -321,16 +319,16 @@ __global__ __launch_bounds__(LT) void long_pass_kernel(const float* __restrict__
         TL = fma(x, dn[e] ? 1.0 : 0.0, TL);
       }
     }
-    if (__any(any_in)) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint64_t m = __ballot(in[e]);
-        const int at = staged + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
-                                    static_cast<uint32_t>(m >> 32),
-                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
-        if (in[e] & (at < kStage)) stage[wid][at] = v[e];
-        staged += __popcll(m);
-      }
+    // members, one per lane and turn (a lane seldom holds two)
+    uint32_t mem = (in[0] ? 1u : 0u) | (in[1] ? 2u : 0u) | (in[2] ? 4u : 0u) | (in[3] ? 8u : 0u);
+    for (uint64_t m = __ballot(mem != 0u); m != 0ull; m = __ballot(mem != 0u)) {
+      const int at = staged + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+                                  static_cast<uint32_t>(m >> 32),
+                                  __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
+      const float x = (mem & 1u) ? v[0] : ((mem & 2u) ? v[1] : ((mem & 4u) ? v[2] : v[3]));
+      if ((mem != 0u) & (at < kStage)) stage[wid][at] = x;
+      mem &= mem - 1u;
+      staged += __popcll(m);
     }
   };
   // steps of kLongQuads 16-byte loads per thread, the next step's issued
@@ -865,11 +863,11 @@ __global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
 // --------------------------------------------------------------- launches --
 namespace {
 // Rows past 2^24 scores take four times the sample, which halves the window.
-// Rows past 2^22 scores take 256 cells (a window can hold several percent of
-// the row, and long_root takes three cells of it), up to 512 blocks and the
-// separate merge; shorter rows 64 cells, up to 256 blocks, and merge them in
-// long_root.
-bool long_wide(int64_t n) { return n > (int64_t(1) << 22); }
+// Rows past 2^18 scores take 256 cells and the separate merge (a window can
+// hold several percent of the row, of which long_root takes three cells: at
+// 2^20 with 64 cells up to 2900 members, 35 us of narrowing instead of 12),
+// and past 2^22 up to 512 blocks; shorter rows 64 cells, merged in long_root.
+bool long_wide(int64_t n) { return n > (int64_t(1) << 18); }
 int long_cells(int64_t n) { return long_wide(n) ? 256 : 64; }
 
 struct LongGrid {
@@ -880,7 +878,7 @@ struct LongGrid {
 // batch takes fewer and longer chunks per row, so that the grid stays a few
 // rounds of the device and long_root has fewer blocks to merge.
 LongGrid long_grid(int64_t rows, int64_t n) {
-  const int64_t most = long_wide(n) ? kLongMaxBlocks : kLongMaxBlocks / 2;
+  const int64_t most = n > (int64_t(1) << 22) ? kLongMaxBlocks : kLongMaxBlocks / 2;
   int64_t cap = rows > 1 ? 768 / rows : most;
   cap = cap < 8 ? 8 : (cap > most ? most : cap);
   int64_t chunk = (n + cap - 1) / cap;

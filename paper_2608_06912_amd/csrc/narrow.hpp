@@ -85,6 +85,26 @@ __device__ double narrow_solve(Each&& each, uint32_t total, uint32_t weight, con
   uint32_t left = total;
   float x = x0;
   int same = 0, last = 0;
+  // the set's range, where the middle of an end still open is taken
+  float mn = INFINITY, mx = -INFINITY;
+  if (left > static_cast<uint32_t>(kNarrowMax)) {
+    each([&](float v, uint32_t) {
+      mn = fminf(mn, v);
+      mx = fmaxf(mx, v);
+    });
+    mn = wave_min(mn, INFINITY);
+    mx = wave_max(mx, -INFINITY);
+    if (lane == 0) {
+      sm.um[wid] = mn;
+      sm.vm[wid] = mx;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      mn = fminf(mn, sm.um[w]);
+      mx = fmaxf(mx, sm.vm[w]);
+    }
+  }
   for (int it = 0; left > static_cast<uint32_t>(kNarrowMax) && it < 96; ++it) {
     const int pb = it & 1;   // two sets of partials: one barrier per point
     double P = 0.0, E = 0.0;
@@ -147,7 +167,8 @@ __device__ double narrow_solve(Each&& each, uint32_t total, uint32_t weight, con
       const double step = t * (f - k) / F * static_cast<double>(1 << (same < 6 ? same : 6));
       xn = static_cast<float>(xd + step);
     }
-    if (!(xn > lo && xn < hi)) xn = middle(lo, hi, it);
+    if (!(xn > lo && xn < hi)) xn = middle(fmaxf(lo, mn), fminf(hi, mx), it);
+    if (!(xn > lo && xn < hi)) xn = key_mid(lo, hi);
     x = xn;
     if (!(x > lo && x < hi)) break;   // no float between the ends
   }
