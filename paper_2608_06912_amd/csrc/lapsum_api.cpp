@@ -672,13 +672,14 @@ bool forward_on_chip(int64_t batch, int64_t n) {
 }
 
 // Short rows take a wave each where that is faster than a workgroup each:
-// always up to 256 scores (one row 8 against 11 us, 4096 rows of 256 19.5
-// against 161), and up to kRowWaveMax from 512 rows on, when the workgroups
-// no longer run all at once (256 rows: 512 scores 15-21 against 12 us, 1024
-// scores 19-32 against 12; 1024 rows of 1024: 26-32 against 44, 2048 of 512:
-// 19-24 against 83).
+// always up to 256 scores (one row 8 against 11 us, 4096 rows of 256 19
+// against 161), and up to kRowWaveMax once the workgroups no longer run all
+// at once: from 512 rows up to 512 scores (512 rows of 512, forward and
+// backward: 15-22 against 24 us; 256 rows alone: even), from 1024 rows above
+// (1024 rows of 1024: 21-29 against 44; 512 rows, forward and backward: 21-32
+// against 26).
 bool row_per_wave(int64_t batch, int64_t n) {
-  return n <= 256 || (n <= kRowWaveMax && batch >= 512);
+  return n <= 256 || (n <= 512 && batch >= 512) || (n <= kRowWaveMax && batch >= 1024);
 }
 
 // Rows on chip, no order wanted.

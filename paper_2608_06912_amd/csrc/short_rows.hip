@@ -1,15 +1,19 @@
 // Forward of short rows (n <= kRowWaveMax), one wave per row, four rows per
 // workgroup: the row in registers, LapSum evaluated at points x until no
-// score is left strictly between the two tightest ones (Newton steps, longer
-// while the root stays on one side, kept inside the ends), the sums of both
+// score is left strictly between the two tightest ones (from about the
+// budget's quantile; Newton steps, longer while the root stays on one side,
+// kept inside the ends; where the temperature is too small for them, between
+// the ends in proportion to LapSum), the sums of both
 // sides then taken relative to the nearest score on each side and the gap
 // solved in closed form; p from the registers.  No LDS and no barriers: the
 // bucketed row kernel spends about 8 us of a workgroup clearing and scanning
 // 2048 buckets whatever the row's length, two workgroups to a CU.
 //
 // Bound: vector issue, about 200 instructions per point and wave at four
-// scores per lane (half of them the float64 sums over the wave) and six to
-// eight points.  4096 rows of 256 scores (k = 16, t = 1): 140 -> 11 us.
+// scores per lane (half of them the float64 sums over the wave) and five to
+// eight points.  4096 rows of 256 scores (k = 16, t = 1): 140 -> 11 us.  At
+// t = 0.02 the start and the proportional points took 256 rows of 256 with
+// k = 0.26 from 24.5 to 15.2 us (backward included, bisection before).
 #include <math.h>
 
 #include "kernels.hpp"
@@ -26,7 +30,8 @@ constexpr int RW = RT / kWave;   // rows per workgroup
 template <int ITEMS>
 __global__ __launch_bounds__(RT) void row_wave_forward_kernel(const float* __restrict__ scores,
                                                               int64_t batch, int n, double k,
-                                                              double t, float* __restrict__ probs,
+                                                              double t, float cut,
+                                                              float* __restrict__ probs,
                                                               double* __restrict__ b_out) {
   const int lane = lane_id();
   const int64_t row = static_cast<int64_t>(blockIdx.x) * RW + threadIdx.x / kWave;
@@ -50,7 +55,10 @@ __global__ __launch_bounds__(RT) void row_wave_forward_kernel(const float* __res
   mn = wave_min(mn, INFINITY);
   mx = wave_max(mx, -INFINITY);
   float lo = -INFINITY, hi = INFINITY;
-  float x = 0.5f * mn + 0.5f * mx;
+  // from about the quantile of the budget's share in a bell-shaped row
+  float x = mx - (mx - mn) * cut;
+  if (!(x > mn && x < mx)) x = 0.5f * mn + 0.5f * mx;
+  double flo = n, fhi = 0.0;   // LapSum at the ends (about, until they are points)
   int same = 0, last = 0;
   uint32_t left = 1u;
   for (int it = 0; it < 96; ++it) {
@@ -73,10 +81,12 @@ __global__ __launch_bounds__(RT) void row_wave_forward_kernel(const float* __res
     int side;
     if (f <= k) {
       hi = x;
+      fhi = f;
       left = na;
       side = 1;
     } else {
       lo = x;
+      flo = f;
       left = ng;
       side = -1;
     }
@@ -87,6 +97,21 @@ __global__ __launch_bounds__(RT) void row_wave_forward_kernel(const float* __res
     const double F = 0.5 * (P + E);
     if (it < 12 && F > 0.0)
       xn = static_cast<float>(xd + t * (f - k) / F * static_cast<double>(1 << (same < 6 ? same : 6)));
+    if (left <= 4u && !(xn > lo && xn < hi)) {
+      // few scores left and no Newton step: one of them, which settles it and
+      // all on one side of it
+      float m = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) m = fmaxf(m, (v[i] > lo) & (v[i] < hi) ? v[i] : -INFINITY);
+      xn = wave_max(m, -INFINITY);
+    }
+    if (!(xn > lo && xn < hi) && (it & 1) == 0) {
+      // where the temperature is too small for a Newton step, between the ends
+      // in proportion to LapSum; every second time their middle
+      const float l = fmaxf(lo, mn), h = fminf(hi, mx);
+      const float s = static_cast<float>((flo - k) / (flo - fhi));
+      xn = l + (h - l) * fminf(fmaxf(s, 0.05f), 0.95f);
+    }
     if (!(xn > lo && xn < hi)) xn = middle(fmaxf(lo, mn), fminf(hi, mx), it);
     if (!(xn > lo && xn < hi)) xn = key_mid(lo, hi);
     x = xn;
@@ -138,9 +163,11 @@ hipError_t launch_row_wave_forward(const float* scores, int64_t batch, int64_t n
   if (n < 1 || n > kRowWaveMax || batch < 1) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>((batch + RW - 1) / RW)), block(RT);
   const int ni = static_cast<int>(n);
+  const double q = k / static_cast<double>(n);
+  const float cut = static_cast<float>(q < 0.5 ? 0.66 * pow(q, 0.4) : 1.0 - 0.66 * pow(1.0 - q, 0.4));
   { ProfScope ps_("row_wave_forward", s);
 #define LAPSUM_ROWW(IT) \
-  hipLaunchKernelGGL(row_wave_forward_kernel<IT>, grid, block, 0, s, scores, batch, ni, k, t, p, b)
+  hipLaunchKernelGGL(row_wave_forward_kernel<IT>, grid, block, 0, s, scores, batch, ni, k, t, cut, p, b)
   if (n <= 64) {
     LAPSUM_ROWW(1);
   } else if (n <= 128) {
