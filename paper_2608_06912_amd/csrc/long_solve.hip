@@ -118,9 +118,13 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
 // below b when S - mu exceeds z sqrt(V mu/S) + z^2/3 and above it when mu - S
 // does (Bernstein's bound for a sum whose mean is mu, z = 5.5; V mu/S the
 // variance scaled to that mean).  Both ends are found together, by Newton
-// steps on S (dS/dx = -F/t) kept inside a bracket, bisection where a step
-// leaves it; a point is taken once the margin is the larger part of its
+// steps on S (dS/dx = -F/t) kept inside a bracket, by interpolating the logit
+// of S between the bracket's ends where a step leaves it (bisection every
+// third time); a point is taken once the margin is the larger part of its
 // distance, so the window is at most about a third wider than it must be.
+// Each point costs about 0.7 us of one workgroup's latency: the start by the
+// logit instead of in the middle takes three points instead of four to six
+// (kernel 13.5 -> 12.8 us at 1e6 scores, 15.6 -> 13.3 for 48 rows of 131073).
 // The sums are float32: they only place the window.
 template <int ITEMS, int NC>
 __global__ __launch_bounds__(WT) void long_window_kernel(const float* __restrict__ scores,
@@ -209,28 +213,54 @@ __global__ __launch_bounds__(WT) void long_window_kernel(const float* __restrict
   float la = mn, lb = mx, ha = mx, hb = mn;
   const bool has_lo = A.S - A.m >= mu, has_hi = B.S + B.m <= mu;
   bool lo_on = has_lo, hi_on = has_hi;
-  float xa = 0.5f * mn + 0.5f * mx, xb = xa;
+  // a point between p and q where the sum's logit, nearly straight over a
+  // bell-shaped row, passes the wanted one's
+  auto logit = [&](float S) {
+    const float c = fminf(fmaxf(S, 0.25f), M - 0.25f);
+    return __log2f(c / (M - c));
+  };
+  auto between = [&](float p, float Lp, float q, float Lq, float want) {
+    const float s = (Lp - logit(want)) / (Lp - Lq);
+    const float x = p + (q - p) * fminf(fmaxf(s, 0.02f), 0.98f);
+    return x > fminf(p, q) && x < fmaxf(p, q) ? x : 0.5f * p + 0.5f * q;
+  };
+  // a Newton step from x that goes at most a quarter of the way to an end of
+  // (l, h): from where few scores are left it can throw far past the root
+  auto near = [](float nx, float x, float l, float h) {
+    return nx > l && nx < h && nx >= l + 0.75f * (x - l) && nx <= h - 0.75f * (h - x);
+  };
+  float Lla = logit(A.S), Llb = logit(B.S), Lha = Llb, Lhb = Lla;
+  const float m0 = 1.15f * (Z * sqrtf(mu * fmaxf(1.0f - mu / M, 0.0f)) + Z2);
+  float xa = between(la, Lla, lb, Llb, mu + m0), xb = between(ha, Lha, hb, Lhb, mu - m0);
   for (int it = 1; it <= 28 && (lo_on || hi_on); ++it) {
     eval(xa, xb, it & 1, A, B);
     if (lo_on) {
       if (A.S - A.m >= mu) {
         la = xa;
+        Lla = logit(A.S);
         lo_on = A.S - mu > 1.35f * A.m;
       } else {
         lb = xa;
+        Llb = logit(A.S);
       }
       const float nx = xa + tf * (A.S - mu - 1.15f * A.m) / A.F;
-      xa = (it < 12 && nx > la && nx < lb) ? nx : 0.5f * la + 0.5f * lb;
+      xa = (it < 12 && near(nx, xa, la, lb)) ? nx
+           : (it % 3 != 0)                  ? between(la, Lla, lb, Llb, mu + 1.15f * A.m)
+                                            : 0.5f * la + 0.5f * lb;
     }
     if (hi_on) {
       if (B.S + B.m <= mu) {
         ha = xb;
+        Lha = logit(B.S);
         hi_on = mu - B.S > 1.35f * B.m;
       } else {
         hb = xb;
+        Lhb = logit(B.S);
       }
       const float nx = xb + tf * (B.S - mu + 1.15f * B.m) / B.F;
-      xb = (it < 12 && nx < ha && nx > hb) ? nx : 0.5f * ha + 0.5f * hb;
+      xb = (it < 12 && near(nx, xb, hb, ha)) ? nx
+           : (it % 3 != 0)                  ? between(ha, Lha, hb, Lhb, mu - 1.15f * B.m)
+                                            : 0.5f * ha + 0.5f * hb;
     }
   }
   if (tid == 0) {

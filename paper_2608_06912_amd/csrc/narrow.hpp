@@ -85,6 +85,8 @@ __device__ double narrow_solve(Each&& each, uint32_t total, uint32_t weight, con
   uint32_t left = total;
   float x = x0;
   int same = 0, last = 0;
+  // LapSum at the ends (about, until they are points)
+  double flo = ext.rank0 + static_cast<double>(weight), fhi = ext.rank0;
   // the set's range, where the middle of an end still open is taken
   float mn = INFINITY, mx = -INFINITY;
   if (left > static_cast<uint32_t>(kNarrowMax)) {
@@ -149,23 +151,31 @@ __device__ double narrow_solve(Each&& each, uint32_t total, uint32_t weight, con
     int side;
     if (f <= k) {
       hi = x;
+      fhi = f;
       left = na;
       side = 1;
     } else {
       lo = x;
+      flo = f;
       left = ng;
       side = -1;
     }
     same = side == last ? same + 1 : 0;
     last = side;
     // the next point: a Newton step, longer each time the root stayed on the
-    // same side so that both ends close in; a middle of the ends when that
-    // leaves them, and after a dozen points always
+    // same side so that both ends close in; when that leaves them (a
+    // temperature too small for it), and after a dozen points always, between
+    // the ends in proportion to LapSum, every second time their middle
     float xn = x;
     const double F = 0.5 * (P + E);
     if (it < 12 && F > 0.0) {
       const double step = t * (f - k) / F * static_cast<double>(1 << (same < 6 ? same : 6));
       xn = static_cast<float>(xd + step);
+    }
+    if (!(xn > lo && xn < hi) && (it & 1) == 0) {
+      const float l = fmaxf(lo, mn), h = fminf(hi, mx);
+      const float q = static_cast<float>((flo - k) / (flo - fhi));
+      xn = l + (h - l) * fminf(fmaxf(q, 0.05f), 0.95f);
     }
     if (!(xn > lo && xn < hi)) xn = middle(fmaxf(lo, mn), fminf(hi, mx), it);
     if (!(xn > lo && xn < hi)) xn = key_mid(lo, hi);
