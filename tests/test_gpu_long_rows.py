@@ -75,6 +75,22 @@ def test_long_row_past_the_entries_kept_on_chip(lib):
         _check(r, k, -0.5, _np(p), float(_np(b)[0]), k)
 
 
+@pytest.mark.parametrize("n", [70001, 3_000_001])
+@pytest.mark.parametrize("dist", ["exponential", "normal", "levels", "outliers"])
+def test_long_row_past_the_sample(lib, n, dist):
+    """Budgets (and their complements) of up to four sampled scores, where b
+    may lie beyond every score of the sample."""
+    rng = np.random.default_rng([n, len(dist)])
+    r = rng.exponential(size=n).astype(np.float32) if dist == "exponential" else _row(dist, n, rng)
+    for mu in (0.05, 0.7, 2.9, 4.0):
+        k = mu * n / 4096.0
+        for sign, kk in ((1.0, k), (-1.0, n - k)):
+            x = (sign * r).astype(np.float32)
+            for alpha in (-0.01, -0.5):
+                p, b = lib.lapsum_forward(_t(x), kk, alpha)
+                _check(x, kk, alpha, _np(p), float(_np(b)[0]), (n, dist, mu, sign, alpha))
+
+
 @pytest.mark.parametrize("batch,n", [(3, 32771), (70, 32769), (5, 400001)])
 def test_long_rows_of_a_batch(lib, batch, n):
     rng = np.random.default_rng([batch, n])
