@@ -183,11 +183,22 @@ hipError_t launch_emit(const float* r, int64_t rows, int64_t n, const double* b_
 
 // Threshold of `rows` consecutive long rows without sorting them
 // (long_solve.hip), b[rows]; n >= 16385 (the sample's strata), rows <= 65535.
-// ws: long_solve_bytes(rows, n) bytes, 256-byte aligned, content irrelevant.
+// A batch is solved in groups of `group` rows, the last of them shorter: the
+// workspace is laid out for `group` rows in every one, since a shorter group
+// laid out by itself could take longer chunks and with them more memory.
+// ws: ws_bytes >= long_solve_bytes(group, n), 256-byte aligned, content
+// irrelevant; hipErrorInvalidValue, and nothing launched, where the rows
+// would not fit.  long_group_bytes: how far `rows` rows of such a group reach.
 constexpr int kLongMaxBlocks = 512;   // blocks a row's streaming pass takes
+// Rows of a batch solved by one set of launches: as many as fit in 48 MiB of
+// workspace (every row of a batch up to there, one row always).  The
+// workspace of a batch therefore stays within that bound or what one row's
+// sort takes, whichever is more.
+int64_t long_rows(int64_t batch, int64_t n);
 size_t long_solve_bytes(int64_t rows, int64_t n);
-hipError_t launch_long_solve(const float* scores, int64_t rows, int64_t n, double k, double t,
-                             void* ws, double* b, hipStream_t s);
+size_t long_group_bytes(int64_t group, int64_t rows, int64_t n);
+hipError_t launch_long_solve(const float* scores, int64_t rows, int64_t group, int64_t n, double k,
+                             double t, void* ws, size_t ws_bytes, double* b, hipStream_t s);
 
 // Device-wide backward for `rows` consecutive rows of n: partial sums per
 // block, reduced in a fixed order to coef[0] = <g, q> and coef[1] = 1/t (0

@@ -118,18 +118,6 @@ struct FullWs {
   SortBuffers sb;   // the permutation's sort, before the solve
 };
 
-// Rows solved by one set of launches: as many as fit in kLongRowsBytes of
-// workspace (every row of a batch up to there, one row always).  The
-// workspace of a batch therefore stays within that bound or what one row's
-// sort takes, whichever is more.
-constexpr size_t kLongRowsBytes = size_t(48) << 20;
-
-int64_t long_rows(int64_t batch, int64_t n) {
-  int64_t rows = batch < 1024 ? batch : 1024;
-  while (rows > 1 && long_solve_bytes(rows, n) > kLongRowsBytes) rows -= (rows + 15) / 16;
-  return rows < 1 ? 1 : rows;
-}
-
 FullWs carve_full(Carve& c, int64_t batch, int64_t n, bool with_vals) {
   FullWs w{};
   w.sb.keys[0] = c.take<uint32_t>(n);
@@ -154,9 +142,10 @@ FullWs carve_full(Carve& c, int64_t batch, int64_t n, bool with_vals) {
 int long_forward(const float* scores, int64_t batch, int64_t n, double k, double t, float* p,
                  double* b, void* ws, hipStream_t s) {
   const int64_t step = long_rows(batch, n);
+  const size_t ws_bytes = long_solve_bytes(step, n);
   for (int64_t row = 0; row < batch; row += step) {
     const int64_t rows = batch - row < step ? batch - row : step;
-    LAPSUM_TRY(launch_long_solve(scores + row * n, rows, n, k, t, ws, b + row, s));
+    LAPSUM_TRY(launch_long_solve(scores + row * n, rows, step, n, k, t, ws, ws_bytes, b + row, s));
     LAPSUM_TRY(launch_emit(scores + row * n, rows, n, b + row, t, p + row * n, s));
   }
   return LAPSUM_OK;
@@ -844,8 +833,8 @@ int lapsum_hard_mask(const float* scores, int64_t batch, int64_t n, int64_t k, f
     } else {
       const int64_t ls = long_rows(batch, n);
       for (int64_t q = 0; q < rows; q += ls)
-        LAPSUM_TRY(launch_long_solve(r + q * n, rows - q < ls ? rows - q : ls, n, kh, kHardT, ws,
-                                     b + q, stream));
+        LAPSUM_TRY(launch_long_solve(r + q * n, rows - q < ls ? rows - q : ls, ls, n, kh, kHardT, ws,
+                                     long_solve_bytes(ls, n), b + q, stream));
     }
     LAPSUM_TRY(launch_hard_mask(r, rows, n, k, b, counts, m, stream));
   }

@@ -934,8 +934,8 @@ T* carve(char* base, size_t& off, size_t count) {
   return p;
 }
 
-LongCells long_view(void* ws, int64_t rows, int64_t n, size_t* bytes) {
-  const LongGrid lg = long_grid(rows, n);
+// Laid out for `rows` rows of the grid `lg`.
+LongCells long_view(void* ws, int64_t rows, const LongGrid& lg, int64_t n, size_t* bytes) {
   const size_t slots = static_cast<size_t>(rows) * static_cast<size_t>(lg.G);
   const size_t NC = static_cast<size_t>(long_cells(n));
   char* base = static_cast<char*>(ws);
@@ -958,16 +958,32 @@ LongCells long_view(void* ws, int64_t rows, int64_t n, size_t* bytes) {
 
 size_t long_solve_bytes(int64_t rows, int64_t n) {
   size_t bytes = 0;
-  long_view(nullptr, rows, n, &bytes);
+  long_view(nullptr, rows, long_grid(rows, n), n, &bytes);
   return bytes;
 }
 
-hipError_t launch_long_solve(const float* scores, int64_t rows, int64_t n, double k, double t,
-                             void* ws, double* b, hipStream_t s) {
-  if (rows < 1 || rows > 65535 || n < 1) return hipErrorInvalidValue;
+int64_t long_rows(int64_t batch, int64_t n) {
+  constexpr size_t most = size_t(48) << 20;
+  int64_t rows = batch < 1024 ? batch : 1024;
+  while (rows > 1 && long_solve_bytes(rows, n) > most) rows -= (rows + 15) / 16;
+  return rows < 1 ? 1 : rows;
+}
+
+size_t long_group_bytes(int64_t group, int64_t rows, int64_t n) {
+  const LongGrid lg = long_grid(group, n);
+  // (the lists come last, and a row's follow the row's before it)
+  const size_t unused = static_cast<size_t>(group - rows) * static_cast<size_t>(lg.G) *
+                        static_cast<size_t>(lg.chunk) * sizeof(float);
+  return long_solve_bytes(group, n) - unused;
+}
+
+hipError_t launch_long_solve(const float* scores, int64_t rows, int64_t group, int64_t n, double k,
+                             double t, void* ws, size_t ws_bytes, double* b, hipStream_t s) {
+  if (rows < 1 || rows > group || group > 65535 || n < 1) return hipErrorInvalidValue;
+  if (long_group_bytes(group, rows, n) > ws_bytes) return hipErrorInvalidValue;
+  const LongGrid lg = long_grid(group, n);
   size_t bytes = 0;
-  const LongCells o = long_view(ws, rows, n, &bytes);
-  const LongGrid lg = long_grid(rows, n);
+  const LongCells o = long_view(ws, group, lg, n, &bytes);
   const unsigned ry = static_cast<unsigned>(rows);
   const bool wide = long_wide(n);
   { ProfScope ps_("long_window", s);

@@ -200,3 +200,29 @@ def test_bracketed_workspace_has_a_slice_per_row_in_flight():
     # with the M indices the rows go one after another through one slice
     assert L.lapsum_forward_bracketed_workspace_size(9, 100000, 2000, 5000, True) == \
         L.lapsum_forward_bracketed_workspace_size(1, 100000, 2000, 5000, True)
+
+
+def test_every_group_of_a_batch_fits_the_workspace():
+    """Long rows of a batch are solved a group at a time; the last, shorter
+    group must not reach past the workspace sized for a whole one.  (Laid out
+    for itself it took up to 3.5 MB more: 839 rows of 163841.)"""
+    import random
+    lib = ctypes.CDLL(L.LIB_PATH)
+    i64 = ctypes.c_int64
+    rows = lib._ZN6lapsum9long_rowsEll
+    rows.argtypes, rows.restype = [i64, i64], i64
+    need = lib._ZN6lapsum16long_group_bytesElll
+    need.argtypes, need.restype = [i64, i64, i64], ctypes.c_size_t
+    rng = random.Random(7)
+    cases = [(59, 358858), (59, 359207), (278, 163841), (839, 163841), (238, 200000),
+             (1189, 165853), (116, 272601), (70, 32769), (3, 40000000)]
+    cases += [(rng.randint(2, 2048), int(32769 * 12 ** rng.random())) for _ in range(3000)]
+    groups = 0
+    for batch, n in cases:
+        step = rows(batch, n)
+        assert 1 <= step <= batch
+        have = min(L.lapsum_forward_workspace_size(batch, n), L.lapsum_hard_mask_workspace_size(batch, n))
+        for group in {step, batch % step or step}:
+            assert need(step, group, n) <= have, (batch, n, step, group)
+            groups += group < step
+    assert groups > 1000

@@ -101,6 +101,28 @@ def test_long_rows_of_a_batch(lib, batch, n):
         _check(r[i], n / 20.0, -0.1, p[i], float(b[i]), (batch, n, i))
 
 
+def test_last_group_of_a_batch_stays_in_its_workspace(lib):
+    """59 rows are solved in groups of 30 and 29: an exact workspace with a
+    guard behind it, forward and hard mask."""
+    import torch
+    batch, n, guard = 59, 358858, 4 << 20
+    gen = torch.Generator(device="cuda").manual_seed(59)
+    x = torch.randn(batch, n, generator=gen, device="cuda")
+    k = n // 20
+    for size, call in ((lib.lapsum_forward_workspace_size(batch, n),
+                        lambda ws: lib.lapsum_forward(x, float(k), -1.0, workspace=ws)),
+                       (lib.lapsum_hard_mask_workspace_size(batch, n),
+                        lambda ws: lib.lapsum_hard_mask(x, k, workspace=ws))):
+        buf = torch.full((size + guard,), 0x5a, dtype=torch.uint8, device="cuda")
+        out = call(buf[:size])
+        assert bool((buf[size:] == 0x5a).all())
+        if isinstance(out, tuple):
+            for i in (0, 29, 30, 58):
+                _check(_np(x[i]), float(k), -1.0, _np(out[0][i]), float(_np(out[1])[i]), i)
+        else:
+            assert bool((out.sum(1) == k).all())
+
+
 def _sample_positions(n, m=4096):
     """Where the window's sample reads (one hashed position per stratum)."""
     s = np.arange(m, dtype=np.uint64)
