@@ -83,6 +83,13 @@ struct FullNode : public torch::autograd::Function<FullNode> {
     const Tensor p = ctx->get_saved_variables()[0].detach();
     Tensor g = grads[0];
     if (!g.defined()) return variable_list(6);
+    // (a saved-tensor hook can hand back any tensor; the kernels read p as
+    // dense float32 rows in device memory)
+    TORCH_CHECK_VALUE(p.is_cuda() && p.device() == g.device(),
+                      "the saved p must be a CUDA (HIP) tensor on the gradient's device");
+    TORCH_CHECK_VALUE(p.scalar_type() == at::kFloat, "the saved p must be float32");
+    TORCH_CHECK_VALUE(p.layout() == at::kStrided && p.dim() >= 1 && p.is_contiguous(),
+                      "the saved p must be contiguous");
     const c10::DeviceGuard guard(p.device());
     const at::AutoDispatchBelowADInplaceOrView below;
     if (g.scalar_type() != at::kFloat) g = g.to(at::kFloat);

@@ -80,3 +80,27 @@ def test_native_node_leaves_transforms_and_errors_to_the_python_node(lib):
     with torch.autograd.graph.saved_tensors_hooks(lambda t: packed.append(t.shape) or t, lambda t: t):
         A.soft_topk(x.requires_grad_(), 10.0, -1.0).sum().backward()
     assert torch.Size([4, 100]) in packed
+
+
+@pytest.mark.parametrize("unpack", ["cpu", "strided", "float64", "shape"])
+def test_native_node_refuses_another_saved_tensor(lib, unpack):
+    """What a saved-tensor hook hands back is checked before a kernel reads it."""
+    import torch
+
+    import paper_2608_06912_amd.autograd as A
+    change = {"cpu": lambda t: t.cpu(), "float64": lambda t: t.double(),
+              "strided": lambda t: torch.cat([t, t], 1)[:, ::2],
+              "shape": lambda t: t[:2]}[unpack]
+    x = torch.randn(4, 100, device="cuda", requires_grad=True)
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t, change):
+        out = A.soft_topk(x, 10.0, -1.0)
+        with pytest.raises(RuntimeError if unpack == "shape" else ValueError):
+            out.sum().backward()
+    assert x.grad is None
+    # one that hands the values back unchanged is as good as none
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t.cpu(), lambda t: t.cuda()):
+        A.soft_topk(x, 10.0, -1.0).sum().backward()
+    kept = x.grad.clone()
+    x.grad = None
+    A.soft_topk(x, 10.0, -1.0).sum().backward()
+    assert torch.equal(x.grad, kept)
