@@ -27,7 +27,7 @@ import os
 
 import torch
 
-from . import (HERE, LapsumError, lapsum_backward, lapsum_backward_band, lapsum_bracket_noise,
+from . import (HERE, lapsum_backward, lapsum_backward_band, lapsum_bracket_noise,
                lapsum_forward, lapsum_forward_bracketed, lapsum_hard_mask, load, new_band)
 
 __all__ = ["soft_topk", "hard_topk_mask", "straight_through", "choose_path", "sample_size",
@@ -215,13 +215,7 @@ def _native_full(scores, k, alpha, ste=False):
     kf = float(k.item() if kt else k)
     af = float(alpha.item() if at else alpha)
     node = _node or _load_node()
-    try:
-        return node.full(scores, k if kt else None, alpha if at else None, kf, af, ste)
-    except RuntimeError:
-        status = node.last_status()
-        if status:
-            raise LapsumError(status, "lapsum_forward") from None
-        raise
+    return node.full(scores, k if kt else None, alpha if at else None, kf, af, ste)
 
 
 def straight_through(p, m):

@@ -13,8 +13,9 @@
 #include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
 #include <c10/core/DeviceGuard.h>
 
-#include <string>
-#include <vector>
+#include <torch/csrc/Exceptions.h>
+
+#include <stdexcept>
 
 #include "../../include/lapsum.h"
 
@@ -24,13 +25,21 @@ using torch::Tensor;
 using torch::autograd::AutogradContext;
 using torch::autograd::variable_list;
 
-thread_local int t_status = LAPSUM_OK;   // of the last call that threw here
+// A library call that failed, as the binding's own exception: LapsumError with
+// the status and the entry point's name.
+struct Failed : std::runtime_error {
+  Failed(int status, const char* where) : std::runtime_error(where), status(status) {}
+  int status;
+};
 
 void check(int status, const char* where) {
-  t_status = status;
-  if (status == LAPSUM_OK) return;
-  throw std::runtime_error(std::string(where) + ": " + lapsum_status_string(status) + " (status " +
-                           std::to_string(status) + ")");
+  if (status != LAPSUM_OK) throw Failed(status, where);
+}
+
+// Sets it as the current Python error (with the GIL held).
+void set_error(const Failed& f) {
+  const py::object type = py::module_::import("paper_2608_06912_amd").attr("LapsumError");
+  PyErr_SetObject(type.ptr(), type(f.status, f.what()).ptr());
 }
 
 hipStream_t stream_of(const Tensor& x) {
@@ -80,6 +89,18 @@ struct FullNode : public torch::autograd::Function<FullNode> {
   }
 
   static variable_list backward(AutogradContext* ctx, variable_list grads) {
+    try {
+      return vjp(ctx, grads);
+    } catch (const Failed& f) {   // on the engine's thread
+      const py::gil_scoped_acquire gil;
+      set_error(f);
+      python_error e;
+      e.persist();
+      throw e;
+    }
+  }
+
+  static variable_list vjp(AutogradContext* ctx, const variable_list& grads) {
     const Tensor p = ctx->get_saved_variables()[0].detach();
     Tensor g = grads[0];
     if (!g.defined()) return variable_list(6);
@@ -141,7 +162,11 @@ struct FullNode : public torch::autograd::Function<FullNode> {
 PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
   m.def("full", [](const Tensor& scores, const std::optional<Tensor>& k_like,
                    const std::optional<Tensor>& alpha_like, double k, double alpha, bool ste) {
-    return FullNode::apply(scores, k_like, alpha_like, k, alpha, ste);
+    try {
+      return FullNode::apply(scores, k_like, alpha_like, k, alpha, ste);
+    } catch (const Failed& f) {
+      set_error(f);
+      throw py::error_already_set();
+    }
   });
-  m.def("last_status", [] { return t_status; });
 }

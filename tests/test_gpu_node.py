@@ -104,3 +104,25 @@ def test_native_node_refuses_another_saved_tensor(lib, unpack):
     x.grad = None
     A.soft_topk(x, 10.0, -1.0).sum().backward()
     assert torch.equal(x.grad, kept)
+
+
+def test_native_node_reports_each_failure_as_its_own(lib):
+    """A rejected call leaves nothing behind: a later torch error (here an
+    allocation past the process's share of memory) surfaces unchanged, on the
+    same thread."""
+    import torch
+
+    import paper_2608_06912_amd.autograd as A
+    x = torch.randn(64, 1 << 16, device="cuda", requires_grad=True)
+    with pytest.raises(lib.LapsumError, match="lapsum_forward") as e:
+        A.soft_topk(x, 0.0, -1.0)
+    assert e.value.status == 1
+    total = torch.cuda.get_device_properties(x.device).total_memory
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(min(1.0, (torch.cuda.memory_reserved() + 1024) / total))
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            A.soft_topk(x, 10.0, -1.0)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert A.soft_topk(x, 10.0, -1.0).shape == x.shape
