@@ -163,6 +163,9 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
   m.def("full", [](const Tensor& scores, const std::optional<Tensor>& k_like,
                    const std::optional<Tensor>& alpha_like, double k, double alpha, bool ste) {
     try {
+      // without the GIL, as a ctypes call runs: an allocation or a launch can
+      // wait for the device
+      const py::gil_scoped_release nogil;
       return FullNode::apply(scores, k_like, alpha_like, k, alpha, ste);
     } catch (const Failed& f) {
       set_error(f);

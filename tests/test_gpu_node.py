@@ -126,3 +126,35 @@ def test_native_node_reports_each_failure_as_its_own(lib):
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert A.soft_topk(x, 10.0, -1.0).shape == x.shape
+
+
+def test_native_node_runs_without_the_gil(lib):
+    """Another Python thread gets to run while the forward is in native code
+    (no thread is made to yield here, so only the call itself can)."""
+    import sys
+    import threading
+
+    import torch
+
+    import paper_2608_06912_amd.autograd as A
+    x = torch.randn(256, 4096, device="cuda")
+    A.soft_topk(x, 10.0, -1.0)
+    ran = []
+    old = sys.getswitchinterval()
+    try:
+        for _ in range(500):
+            go = threading.Event()
+            seen = []
+            t = threading.Thread(target=lambda: (go.wait(), seen.append(1)))
+            t.start()
+            sys.setswitchinterval(1000.0)
+            go.set()
+            A._native_full(x, 10.0, -1.0)
+            ran = list(seen)
+            sys.setswitchinterval(old)
+            t.join()
+            if ran:
+                break
+    finally:
+        sys.setswitchinterval(old)
+    assert ran
