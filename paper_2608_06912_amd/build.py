@@ -12,6 +12,7 @@ extension over liblapsum.so) to _node.so.
 from __future__ import annotations
 
 import concurrent.futures as cf
+import importlib.util
 import os
 import shutil
 import subprocess
@@ -82,33 +83,49 @@ def build(verbose: bool = False, jobs: int | None = None) -> str:
         objs.append(obj)
         work.append(([hipcc, *COMMON, *HOST_FLAGS, f"-I{rocm_inc}", "-c", os.path.join(CSRC, src),
                       "-o", obj], src))
-    node_obj = os.path.join(BUILD, NODE_SOURCE + ".o")
-    work.insert(0, (_node_compile(hipcc, rocm_inc, node_obj), NODE_SOURCE))
     jobs = jobs or min(len(work), max(1, min(8, os.cpu_count() or 1)))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
+        # the node needs torch's headers, the library nothing but HIP: without
+        # torch the library alone is built
+        node = None
+        if importlib.util.find_spec("torch") is not None:
+            node_obj = os.path.join(BUILD, NODE_SOURCE + ".o")
+            node = ex.submit(lambda: _compile((_node_compile(hipcc, rocm_inc, node_obj), NODE_SOURCE)))
         for src in ex.map(_compile, work):
             if verbose:
                 print(f"compiled {src}", flush=True)
-    tmp = LIB + ".tmp"
-    link = [hipcc, "-shared", f"--offload-arch={ARCH}", "-Wl,-soname,liblapsum.so", "-o", tmp, *objs]
-    proc = subprocess.run(link, capture_output=True, text=True)
-    if proc.returncode != 0:
-        raise RuntimeError(f"linking failed:\n{' '.join(link)}\n{proc.stderr}")
-    os.replace(tmp, LIB)
+        _link_library(hipcc, objs)
+        if verbose:
+            print(f"built {LIB}", flush=True)
+        if node is None:
+            print("torch not found: the native autograd node is not built", flush=True)
+            return LIB
+        node.result()
+    _link_node(hipcc, node_obj)
     if verbose:
-        print(f"built {LIB}", flush=True)
+        print(f"compiled {NODE_SOURCE}\nbuilt {NODE}", flush=True)
+    return LIB
+
+
+def _run(cmd: list) -> None:
+    proc = subprocess.run(cmd, capture_output=True, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError(f"linking failed:\n{' '.join(cmd)}\n{proc.stderr}")
+
+
+def _link_library(hipcc: str, objs: list) -> None:
+    tmp = LIB + ".tmp"
+    _run([hipcc, "-shared", f"--offload-arch={ARCH}", "-Wl,-soname,liblapsum.so", "-o", tmp, *objs])
+    os.replace(tmp, LIB)
+
+
+def _link_node(hipcc: str, node_obj: str) -> None:
     import torch
     tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
     tmp = NODE + ".tmp"
-    link = [hipcc, "-shared", "-o", tmp, node_obj, LIB, f"-L{tlib}", "-lc10", "-lc10_hip",
-            "-ltorch_cpu", "-ltorch_python", "-ltorch", "-Wl,-rpath,$ORIGIN"]
-    proc = subprocess.run(link, capture_output=True, text=True)
-    if proc.returncode != 0:
-        raise RuntimeError(f"linking failed:\n{' '.join(link)}\n{proc.stderr}")
+    _run([hipcc, "-shared", "-o", tmp, node_obj, LIB, f"-L{tlib}", "-lc10", "-lc10_hip",
+          "-ltorch_cpu", "-ltorch_python", "-ltorch", "-Wl,-rpath,$ORIGIN"])
     os.replace(tmp, NODE)
-    if verbose:
-        print(f"built {NODE}", flush=True)
-    return LIB
 
 
 if __name__ == "__main__":

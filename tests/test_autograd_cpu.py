@@ -59,3 +59,39 @@ def test_bracket_indices_are_uniform_and_cached():
     assert A.bracket_indices(50000, 1000, "cpu", seed=3) is idx
     counts = np.bincount(idx.numpy(), minlength=1000)
     assert stats.chisquare(counts).pvalue > 1e-3
+
+
+def test_library_builds_without_torch(monkeypatch, tmp_path):
+    """The C library needs no torch: without it the node is left out, and the
+    library is linked all the same."""
+    from paper_2608_06912_amd import build as B
+    cmds = []
+    monkeypatch.setattr(B.importlib.util, "find_spec", lambda name: None)
+    monkeypatch.setattr(B, "BUILD", str(tmp_path))
+    monkeypatch.setattr(B, "LIB", str(tmp_path / "liblapsum.so"))
+    monkeypatch.setattr(B, "_compile", lambda job: cmds.append(job[1]) or job[1])
+
+    def run(cmd):
+        cmds.append("link")
+        open(cmd[cmd.index("-o") + 1], "w").close()
+    monkeypatch.setattr(B, "_run", run)
+    assert B.build() == str(tmp_path / "liblapsum.so")
+    assert cmds[-1] == "link" and cmds.count("link") == 1 and B.NODE_SOURCE not in cmds
+    assert set(cmds[:-1]) == set(B.HIP_SOURCES + B.HOST_SOURCES)
+
+
+def test_missing_node_is_named_once(monkeypatch, tmp_path):
+    """soft_topk without _node.so goes through LapSumFunction, after a warning."""
+    import os
+    import warnings
+
+    import paper_2608_06912_amd as L
+    if not os.path.exists(L.LIB_PATH):
+        pytest.skip("library not built")
+    monkeypatch.setattr(A, "_node", None)
+    monkeypatch.setattr(A, "HERE", str(tmp_path))
+    with pytest.warns(UserWarning, match="_node.so is not built"):
+        assert not A._load_node()
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        assert not A._load_node()
