@@ -29,7 +29,7 @@
  *    On an error nothing has been enqueued, except LAPSUM_ERR_HIP, which can
  *    follow earlier launches of the same call.
  *  - Scores must be finite; NaN or infinite scores give unspecified outputs
- *    (they are not scanned for).
+ *    (they are not scanned for), except in lapsum_hard_mask.
  *  - workspace: caller-owned scratch of at least the size the matching
  *    *_workspace_size function returns, aligned to 256 bytes.  Its content
  *    on entry does not matter.  Two calls that overlap in time (different
@@ -177,8 +177,9 @@ int lapsum_topk_mask(const int32_t* perm, int64_t batch, int64_t n, int64_t k,
 
 /* ------------------------------------------------------------------------
  * The same mask straight from the scores, without the order: the k-th largest
- * score of each row is found as the threshold of a vanishing temperature, and
- * equal scores are taken by index (+0.0 before -0.0, as in perm_out).
+ * score of each row is found by a radix select on the keys of perm_out's
+ * order, and equal keys are taken by index.  Infinite scores take their place
+ * in that order (rows masked with -inf), and every row gets exactly k ones.
  *
  *   scores     [batch, n] float32 input, not overlapping mask
  *   k          integer count of ones per row, 0 <= k <= n

@@ -169,12 +169,12 @@ hipError_t launch_dftopk_backward(const float* g, const float* p, int64_t n, con
 hipError_t launch_topk_mask(const int32_t* perm, int64_t batch, int64_t n, int64_t k, float* mask,
                             hipStream_t s);
 
-// Hard top-k mask of `rows` consecutive rows (hard_mask.hip) from the roots b
-// ([rows]) at the budget k - 1/2 and a vanishing temperature, 0 < k < n.
-// counts: hard_mask_bytes(rows, n).
-size_t hard_mask_bytes(int64_t rows, int64_t n);
-hipError_t launch_hard_mask(const float* scores, int64_t rows, int64_t n, int64_t k,
-                            const double* b, void* counts, float* mask, hipStream_t s);
+// Hard top-k mask of a batch straight from the scores (hard_mask.hip), by a
+// radix select on the sort's keys, 1 <= k <= n.  ws: hard_mask_bytes(batch, n)
+// bytes, 256-byte aligned, content irrelevant.
+size_t hard_mask_bytes(int64_t batch, int64_t n);
+hipError_t launch_hard_mask(const float* scores, int64_t batch, int64_t n, int64_t k, float* mask,
+                            void* ws, hipStream_t s);
 
 // Laplace-CDF emit p = sigma((r - b)/t) for `rows` consecutive rows of n
 // scores, b ([rows]) read from device.

@@ -788,18 +788,9 @@ int lapsum_topk_mask(const int32_t* perm, int64_t batch, int64_t n, int64_t k, f
   return LAPSUM_OK;
 }
 
-// A temperature under which no two distinct float32 scores share a term and
-// every shift of the root vanishes in float32 (t ln n < 1e-57).
-constexpr double kHardT = 1e-60;
-
 size_t lapsum_hard_mask_workspace_size(int64_t batch, int64_t n) {
   if (batch < 1 || n < 1 || n > 2147483647LL) return 0;
-  const int64_t rows = batch < 65535 ? batch : 65535;
-  Carve c(nullptr);
-  c.take<double>(static_cast<size_t>(rows));
-  c.take<char>(hard_mask_bytes(rows, n));
-  if (!forward_on_chip(batch, n)) c.take<char>(long_solve_bytes(long_rows(batch, n), n));
-  return c.size();
+  return hard_mask_bytes(batch, n);
 }
 
 int lapsum_hard_mask(const float* scores, int64_t batch, int64_t n, int64_t k, float* mask,
@@ -815,29 +806,7 @@ int lapsum_hard_mask(const float* scores, int64_t batch, int64_t n, int64_t k, f
                                k == 0 ? 0u : 0x3f800000u, stream));
     return LAPSUM_OK;
   }
-  const bool on_chip = forward_on_chip(batch, n);
-  const int64_t step = batch < 65535 ? batch : 65535;
-  Carve c(workspace);
-  double* b = c.take<double>(static_cast<size_t>(step));
-  char* counts = c.take<char>(hard_mask_bytes(step, n));
-  void* ws = on_chip ? nullptr : c.take<char>(long_solve_bytes(long_rows(batch, n), n));
-  const double kh = static_cast<double>(k) - 0.5;
-  for (int64_t row = 0; row < batch; row += step) {
-    const int64_t rows = batch - row < step ? batch - row : step;
-    const float* r = scores + row * n;
-    float* m = mask + row * n;
-    if (on_chip) {
-      // (the on-chip solves also write p, which the mask then replaces)
-      const int st = rows_on_chip(r, rows, n, kh, kHardT, m, b, stream);
-      if (st != LAPSUM_OK) return st;
-    } else {
-      const int64_t ls = long_rows(batch, n);
-      for (int64_t q = 0; q < rows; q += ls)
-        LAPSUM_TRY(launch_long_solve(r + q * n, rows - q < ls ? rows - q : ls, ls, n, kh, kHardT, ws,
-                                     long_solve_bytes(ls, n), b + q, stream));
-    }
-    LAPSUM_TRY(launch_hard_mask(r, rows, n, k, b, counts, m, stream));
-  }
+  LAPSUM_TRY(launch_hard_mask(scores, batch, n, k, mask, workspace, stream));
   return LAPSUM_OK;
 }
 

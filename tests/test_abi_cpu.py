@@ -221,7 +221,7 @@ def test_every_group_of_a_batch_fits_the_workspace():
     for batch, n in cases:
         step = rows(batch, n)
         assert 1 <= step <= batch
-        have = min(L.lapsum_forward_workspace_size(batch, n), L.lapsum_hard_mask_workspace_size(batch, n))
+        have = L.lapsum_forward_workspace_size(batch, n)
         for group in {step, batch % step or step}:
             assert need(step, group, n) <= have, (batch, n, step, group)
             groups += group < step

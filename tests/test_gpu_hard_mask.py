@@ -41,3 +41,44 @@ def test_hard_mask_rejects_invalid_arguments(lib):
     assert L.lapsum_hard_mask(v(256), 1, 8, 2, v(256), v(0), 0, v(0)) == 1     # overlapping
     assert L.lapsum_hard_mask(v(256), 1, 8, 9, v(512), v(0), 0, v(0)) == 1
     assert L.lapsum_hard_mask(v(256), 1, 8, 2, v(512), v(0), 0, v(0)) == 2     # no workspace
+
+
+@pytest.mark.parametrize("batch,n", [(5, 64), (6, 1024), (5, 1025), (5, 4096), (4, 8193), (4, 32768),
+                                     (1, 32768), (3, 32769), (3, 262147), (1, 1_000_003)])
+def test_hard_mask_of_masked_rows(lib, batch, n):
+    """Rows masked with -inf, the lowest float or another sentinel, with
+    infinite and NaN scores: the order of the keys decides, in every variant,
+    with the budget inside, at and past the masked share."""
+    rng = np.random.default_rng([batch, n, 2])
+    low = np.finfo(np.float32).min
+    for masked in (0.01, 0.3, 0.9):
+        x = rng.standard_normal((batch, n)).astype(np.float32)
+        off = rng.random(x.shape) < masked
+        for i in range(batch):
+            x[i, off[i]] = (-np.inf, low, -1e30, -np.inf, -1e9)[i % 5]
+        if batch > 3:
+            x[3, rng.random(n) < 0.1] = low          # the lowest float above -inf
+            x[3, :3] = (np.inf, np.finfo(np.float32).max, np.inf)
+        if batch > 4:
+            x[4, -3:] = (np.nan, np.inf, -np.nan)
+        t = _t(x)
+        for k in sorted({1, 2, n // 50 + 1, n // 3, int((1 - masked) * n), int(0.95 * n), n - 1}):
+            m = _np(lib.lapsum_hard_mask(t, k))
+            for i in range(batch):
+                ref = np.zeros(n, np.float32)
+                ref[O.desc_order(x[i])[:k]] = 1.0
+                assert np.array_equal(m[i], ref), (n, masked, k, i, int(np.sum(m[i] != ref)))
+
+
+def test_hard_mask_of_many_groups(lib):
+    """A batch taken in several groups, and rows whose ties span the blocks."""
+    import torch
+    batch, n = 150, 131_075
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.randint(-3, 4, (batch, n), generator=gen, device="cuda").float()
+    x[::2] += 0.25 * torch.randn(x[::2].shape, generator=gen, device="cuda")
+    k = n // 3
+    m = lib.lapsum_hard_mask(x, k)
+    assert bool((m.sum(1) == k).all())
+    ref = torch.zeros_like(x).scatter_(1, torch.sort(x, dim=1, descending=True, stable=True)[1][:, :k], 1.0)
+    assert bool((m == ref).all())
