@@ -48,6 +48,8 @@ constexpr int LW = LT / kWave;
 constexpr int kStage = 512;               // members a wave of long_pass stages
 constexpr int kLongQuads = 4;             // 16-byte loads in flight per thread
 constexpr int64_t kLongTile = static_cast<int64_t>(LT) * 4;   // scores per step of a block
+constexpr int kWindowPoints = 14;
+constexpr float kMaxScore = 3.402823466e38f;
 constexpr float kFewSamples = 3.0f;       // (b past the sample's last score: e^-3)
 constexpr int kRootCap = 24576;           // entries long_root narrows in LDS (half with weights)
 
@@ -123,6 +125,14 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
 // of S between the bracket's ends where a step leaves it (bisection every
 // third time); a point is taken once the margin is the larger part of its
 // distance, so the window is at most about a third wider than it must be.
+// Points by value do not come near the root where the row spans many orders
+// of magnitude (scores masked with a sentinel, heavy tails): from the third
+// point on, one that leaves more than three quarters of the samples between
+// the ends is followed by the middle of the keys, which is sensitive to
+// magnitudes.  Rows with 30% of the scores at -3.4e38 take 5-11 points instead
+// of the last, bell-shaped rows 2-4 as without it.  Where no point qualifies
+// after kWindowPoints, the ends are what they are: the cells
+// (and not b) depend on them.
 // Each point costs about 0.7 us of one workgroup's latency: the start by the
 // logit instead of in the middle takes three points instead of four to six
 // (kernel 13.5 -> 12.8 us at 1e6 scores, 15.6 -> 13.3 for 48 rows of 131073).
@@ -147,6 +157,7 @@ __global__ __launch_bounds__(WT) void long_window_kernel(const float* __restrict
     const uint64_t a = static_cast<uint64_t>(s) * static_cast<uint64_t>(n) / M;
     const uint64_t e = static_cast<uint64_t>(s + 1) * static_cast<uint64_t>(n) / M;
     v[i] = r[a + ((static_cast<uint64_t>(mix32(s)) * (e - a)) >> 32)];
+    v[i] = fminf(fmaxf(v[i], -kMaxScore), kMaxScore);   // (every point stays finite)
   }
   float mn = v[0], mx = v[0];
 #pragma unroll
@@ -213,7 +224,12 @@ __global__ __launch_bounds__(WT) void long_window_kernel(const float* __restrict
   eval(mn, mx, 0, A, B);
   float la = mn, lb = mx, ha = mx, hb = mn;
   const bool has_lo = A.S - A.m >= mu, has_hi = B.S + B.m <= mu;
-  bool lo_on = has_lo, hi_on = has_hi;
+  // a root surely past the sample's last score (rows much narrower than t):
+  // the sample has no better end than that score
+  const bool above = has_lo && B.S - B.m >= mu, under = has_hi && A.S + A.m <= mu;
+  if (above) la = mx;
+  if (under) ha = mn;
+  bool lo_on = has_lo && !above, hi_on = has_hi && !under;
   // a point between p and q where the sum's logit, nearly straight over a
   // bell-shaped row, passes the wanted one's
   auto logit = [&](float S) {
@@ -231,37 +247,49 @@ __global__ __launch_bounds__(WT) void long_window_kernel(const float* __restrict
     return nx > l && nx < h && nx >= l + 0.75f * (x - l) && nx <= h - 0.75f * (h - x);
   };
   float Lla = logit(A.S), Llb = logit(B.S), Lha = Llb, Lhb = Lla;
+  float Sla = A.S, Slb = B.S, Sha = B.S, Shb = A.S;
+  bool lo_key = false, hi_key = false;   // the last point was a middle of the keys
   const float m0 = 1.15f * (Z * sqrtf(mu * fmaxf(1.0f - mu / M, 0.0f)) + Z2);
   float xa = between(la, Lla, lb, Llb, mu + m0), xb = between(ha, Lha, hb, Lhb, mu - m0);
-  for (int it = 1; it <= 28 && (lo_on || hi_on); ++it) {
+  for (int it = 1; it <= kWindowPoints && (lo_on || hi_on); ++it) {
     eval(xa, xb, it & 1, A, B);
     if (lo_on) {
+      const float old = Sla - Slb;
       if (A.S - A.m >= mu) {
         la = xa;
+        Sla = A.S;
         Lla = logit(A.S);
         lo_on = A.S - mu > 1.35f * A.m;
       } else {
         lb = xa;
+        Slb = A.S;
         Llb = logit(A.S);
       }
       const float nx = xa + tf * (A.S - mu - 1.15f * A.m) / A.F;
       xa = (it < 12 && near(nx, xa, la, lb)) ? nx
            : (it % 3 != 0)                  ? between(la, Lla, lb, Llb, mu + 1.15f * A.m)
                                             : 0.5f * la + 0.5f * lb;
+      lo_key = it >= 3 && !lo_key && Sla - Slb > 0.75f * old;
+      if (lo_key) xa = key_mid(la, lb);
     }
     if (hi_on) {
+      const float old = Shb - Sha;
       if (B.S + B.m <= mu) {
         ha = xb;
+        Sha = B.S;
         Lha = logit(B.S);
         hi_on = mu - B.S > 1.35f * B.m;
       } else {
         hb = xb;
+        Shb = B.S;
         Lhb = logit(B.S);
       }
       const float nx = xb + tf * (B.S - mu + 1.15f * B.m) / B.F;
       xb = (it < 12 && near(nx, xb, hb, ha)) ? nx
            : (it % 3 != 0)                  ? between(ha, Lha, hb, Lhb, mu - 1.15f * B.m)
                                             : 0.5f * ha + 0.5f * hb;
+      hi_key = it >= 3 && !hi_key && Shb - Sha > 0.75f * old;
+      if (hi_key) xb = key_mid(hb, ha);
     }
   }
   if (tid == 0) {
