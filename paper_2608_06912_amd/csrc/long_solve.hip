@@ -31,6 +31,7 @@
 #include <math.h>
 
 #include "kernels.hpp"
+#include "block_sort.hpp"
 #include "narrow.hpp"
 
 namespace lapsum {
@@ -48,7 +49,7 @@ constexpr int LW = LT / kWave;
 constexpr int kStage = 512;               // members a wave of long_pass stages
 constexpr int kLongQuads = 4;             // 16-byte loads in flight per thread
 constexpr int64_t kLongTile = static_cast<int64_t>(LT) * 4;   // scores per step of a block
-constexpr int kWindowPoints = 14;
+constexpr int kWindowPoints = 16;
 constexpr float kMaxScore = 3.402823466e38f;
 constexpr float kFewSamples = 3.0f;       // (b past the sample's last score: e^-3)
 constexpr int kRootCap = 24576;           // entries long_root narrows in LDS (half with weights)
@@ -59,10 +60,15 @@ constexpr int kRootCap = 24576;           // entries long_root narrows in LDS (h
 struct Window {
   float xlo, xhi;      // -inf / +inf: unbounded
   float xcap, xfloor;
-  float scale;         // cells per unit of value
+  float scale;         // cells per unit of value; negative: cells by a table
   float x0;            // the sample's estimate of b
 };
 
+// Where equal steps would leave one cell with most of the members (many equal
+// scores, clusters, a sentinel inside the window), the cells follow the
+// sample instead: bound[c], non-increasing, is the least score of cell c for
+// c < NC - 1, every bound the same share of the sample's members apart; a
+// value met by several bounds has a cell to itself (see long_window).
 template <int NC>
 __device__ __forceinline__ int cell_of(const Window& w, float v) {
   if (v > w.xcap) return 0;
@@ -74,11 +80,27 @@ __device__ __forceinline__ int cell_of(const Window& w, float v) {
 // A member can lie beyond its edge by the rounding of cell_of; exponents are
 // clamped at 0 there, and the last step takes the members themselves.
 template <int NC>
-__device__ __forceinline__ double edge_of(const Window& w, int c) {
+__device__ __forceinline__ double edge_of(const Window& w, const float* __restrict__ bound, int c) {
   if (c == 0) return w.xhi < INFINITY ? w.xhi : w.xcap;
   if (c == NC) return w.xlo > -INFINITY ? w.xlo : w.xfloor;
+  if (w.scale < 0.0f) return bound[c - 1];
   const double cap = w.xcap, fl = w.xfloor;
   return static_cast<float>(cap - static_cast<double>(c - 1) * ((cap - fl) / static_cast<double>(NC - 2)));
+}
+
+// The cell of v from the cells' upper edges (in a fixed number of steps, so
+// that several searches run side by side).
+template <int NC>
+__device__ __forceinline__ int cell_by_edges(const double* edge, float v) {
+  const double x = v;
+  int c = 0;
+#pragma unroll
+  for (int step = NC / 2; step > 0; step >>= 1) c += x < edge[c + step] ? step : 0;
+  return c;
+}
+template <int NC>
+__device__ __forceinline__ int cell_at(const Window& w, const double* edge, float v) {
+  return w.scale >= 0.0f ? cell_of<NC>(w, v) : cell_by_edges<NC>(edge, v);
 }
 
 // One block's share of a row.
@@ -97,6 +119,7 @@ struct LongCells {
   uint32_t* off;    // [rows][G][NC + 1] first entry of the cell in the block's list
   float* list;      // [rows][G * chunk] entries of each block in cell order
   Window* win;      // [rows]
+  float* bound;     // [rows][NC] the cells' table, where the window says so
   double *mU, *mD;  // [rows][NC] the merged cells (rows of many blocks)
   uint32_t* mcnt;
 };
@@ -126,11 +149,12 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
 // third time); a point is taken once the margin is the larger part of its
 // distance, so the window is at most about a third wider than it must be.
 // Points by value do not come near the root where the row spans many orders
-// of magnitude (scores masked with a sentinel, heavy tails): from the third
+// of magnitude (scores masked with a sentinel, heavy tails): from the fifth
 // point on, one that leaves more than three quarters of the samples between
 // the ends is followed by the middle of the keys, which is sensitive to
-// magnitudes.  Rows with 30% of the scores at -3.4e38 take 5-11 points instead
-// of the last, bell-shaped rows 2-4 as without it.  Where no point qualifies
+// magnitudes.  Rows with 30% of the scores at -3.4e38 take 7-12 points instead
+// of the last; bell-shaped and exponential rows, 2-6 of which settle, as many as without
+// it (from the third point on exponential ones took up to 9).  Where no point qualifies
 // after kWindowPoints, the ends are what they are: the cells
 // (and not b) depend on them.
 // Each point costs about 0.7 us of one workgroup's latency: the start by the
@@ -140,12 +164,16 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
 template <int ITEMS, int NC>
 __global__ __launch_bounds__(WT) void long_window_kernel(const float* __restrict__ scores,
                                                          int64_t n, double k, double t,
-                                                         Window* __restrict__ win) {
+                                                         Window* __restrict__ win,
+                                                         float* __restrict__ bounds) {
   constexpr int M = WT * ITEMS;
   constexpr int W = WT / kWave;
   constexpr float Z = 5.5f, Z2 = Z * Z / 3.0f;
   __shared__ float red[2][6][W];
   __shared__ float mm[2][W];
+  __shared__ uint32_t cnt[NC + 2], crowd[2][W];
+  __shared__ uint32_t sorted[sort_buf_words<WT, 16>()];
+  __shared__ SortSmem<WT> ssm;
   const int tid = threadIdx.x;
   const int lane = lane_id();
   const int wid = tid / kWave;
@@ -247,7 +275,7 @@ __global__ __launch_bounds__(WT) void long_window_kernel(const float* __restrict
     return nx > l && nx < h && nx >= l + 0.75f * (x - l) && nx <= h - 0.75f * (h - x);
   };
   float Lla = logit(A.S), Llb = logit(B.S), Lha = Llb, Lhb = Lla;
-  float Sla = A.S, Slb = B.S, Sha = B.S, Shb = A.S;
+  float Sla = above ? B.S : A.S, Slb = B.S, Sha = under ? A.S : B.S, Shb = A.S;
   bool lo_key = false, hi_key = false;   // the last point was a middle of the keys
   const float m0 = 1.15f * (Z * sqrtf(mu * fmaxf(1.0f - mu / M, 0.0f)) + Z2);
   float xa = between(la, Lla, lb, Llb, mu + m0), xb = between(ha, Lha, hb, Lhb, mu - m0);
@@ -269,8 +297,10 @@ __global__ __launch_bounds__(WT) void long_window_kernel(const float* __restrict
       xa = (it < 12 && near(nx, xa, la, lb)) ? nx
            : (it % 3 != 0)                  ? between(la, Lla, lb, Llb, mu + 1.15f * A.m)
                                             : 0.5f * la + 0.5f * lb;
-      lo_key = it >= 3 && !lo_key && Sla - Slb > 0.75f * old;
-      if (lo_key) xa = key_mid(la, lb);
+      if (it >= 5) {
+        lo_key = !lo_key && Sla - Slb > 0.75f * old;
+        if (lo_key) xa = key_mid(la, lb);
+      }
     }
     if (hi_on) {
       const float old = Shb - Sha;
@@ -288,38 +318,110 @@ __global__ __launch_bounds__(WT) void long_window_kernel(const float* __restrict
       xb = (it < 12 && near(nx, xb, hb, ha)) ? nx
            : (it % 3 != 0)                  ? between(ha, Lha, hb, Lhb, mu - 1.15f * B.m)
                                             : 0.5f * ha + 0.5f * hb;
-      hi_key = it >= 3 && !hi_key && Shb - Sha > 0.75f * old;
-      if (hi_key) xb = key_mid(hb, ha);
+      if (it >= 5) {
+        hi_key = !hi_key && Shb - Sha > 0.75f * old;
+        if (hi_key) xb = key_mid(hb, ha);
+      }
     }
   }
-  if (tid == 0) {
-    Window w;
-    w.xlo = has_lo ? la : -INFINITY;
-    w.xhi = has_hi ? ha : INFINITY;
-    // rounding can only cross the ends of a window without scores; keep both
-    // sides well formed
-    if (!(w.xlo < w.xhi)) {
-      w.xlo = -INFINITY;
-      w.xhi = INFINITY;
-    }
-    w.xcap = fminf(mx, w.xhi);
-    w.xfloor = fmaxf(mn, w.xlo);
-    if (!(w.xfloor <= w.xcap)) w.xfloor = w.xcap;
-    // a budget of fewer than kFewSamples of the sample's scores can have b
-    // beyond its last score, where all the row's scores would be one cell:
-    // cells for as much again (likewise below).  1e7 Laplace scores, k = 2000,
-    // t = 0.01, eight rows: forward 65-170 us, mean 105, without, 64-80, mean
-    // 70, with.  With more of them b is seldom there, and the steps would be
-    // twice as wide for nothing.
-    const float span = w.xcap - w.xfloor;
-    if (!has_hi && has_lo && mu < kFewSamples && w.xcap + span < INFINITY) w.xcap += span;
-    if (!has_lo && has_hi && M - mu < kFewSamples && w.xfloor - span > -INFINITY) w.xfloor -= span;
-    const float width = w.xcap - w.xfloor;
-    w.scale = (width > 0.0f && width < INFINITY) ? static_cast<float>(NC - 2) / width : 0.0f;
-    if (!(w.scale < INFINITY)) w.scale = 0.0f;
-    w.x0 = 0.5f * w.xcap + 0.5f * w.xfloor;
-    win[blockIdx.y] = w;
+  Window w;
+  w.xlo = has_lo ? la : -INFINITY;
+  w.xhi = has_hi ? ha : INFINITY;
+  // rounding can only cross the ends of a window without scores; keep both
+  // sides well formed
+  if (!(w.xlo < w.xhi)) {
+    w.xlo = -INFINITY;
+    w.xhi = INFINITY;
   }
+  w.xcap = fminf(mx, w.xhi);
+  w.xfloor = fmaxf(mn, w.xlo);
+  if (!(w.xfloor <= w.xcap)) w.xfloor = w.xcap;
+  // a budget of fewer than kFewSamples of the sample's scores can have b
+  // beyond its last score, where all the row's scores would be one cell:
+  // cells for as much again (likewise below).  1e7 Laplace scores, k = 2000,
+  // t = 0.01, eight rows: forward 65-170 us, mean 105, without, 64-80, mean
+  // 70, with.  With more of them b is seldom there, and the steps would be
+  // twice as wide for nothing.
+  const float span = w.xcap - w.xfloor;
+  if (!has_hi && has_lo && mu < kFewSamples && w.xcap + span < INFINITY) w.xcap += span;
+  if (!has_lo && has_hi && M - mu < kFewSamples && w.xfloor - span > -INFINITY) w.xfloor -= span;
+  const float width = w.xcap - w.xfloor;
+  w.scale = (width > 0.0f && width < INFINITY) ? static_cast<float>(NC - 2) / width : 0.0f;
+  if (!(w.scale < INFINITY)) w.scale = 0.0f;
+  w.x0 = 0.5f * w.xcap + 0.5f * w.xfloor;
+  // the cells by the sample where equal steps would crowd three neighbouring
+  // ones past what long_root keeps on chip, several times their share.  Looked
+  // at where the window can hold a quarter of the row or four times as much
+  // as that (below, long_root divides a crowded cell itself, in 0.1-0.2 ms; the
+  // look costs 1.5 us, which ordinary rows with wide windows would pay).  A
+  // member's term differs between the ends by (1 - e^{-width/t})/2 next to
+  // one of them up to nearly 1 halfway, which tells about how many there are.
+  auto member = [&](float x) { return x >= w.xlo && x < w.xhi; };
+  const float per = static_cast<float>(static_cast<double>(n) / M);   // scores per sample
+  const float ends = fminf(mx, w.xhi) - fmaxf(mn, w.xlo);
+  const float most = 1.25f * (Sla - Sha) / (1.0f - exp2_fast(-ends * c2));   // (NaN: no width)
+  uint32_t in = 0u, top = 0u;
+  if (most * per > 4.0f * kRootCap || (most * per > kRootCap && 4.0f * most > M)) {
+    for (int c = tid; c < NC + 2; c += WT) cnt[c] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+      if (member(v[i])) atomicAdd(&cnt[1 + cell_of<NC>(w, v[i])], 1u);
+    __syncthreads();
+    if (tid < NC) {
+      in = cnt[tid + 1];
+      top = in + cnt[tid] + cnt[tid + 2];
+    }
+    in = wave_sum(in);
+    top = wave_max_u32(top);
+    if (lane == 0) {
+      crowd[0][wid] = in;
+      crowd[1][wid] = top;
+    }
+    __syncthreads();
+    in = 0u;
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      in += crowd[0][i];
+      top = max(top, crowd[1][i]);
+    }
+  }
+  if (static_cast<float>(top) * per > kRootCap && top > 12u * in / NC + 24u) {
+    // 4096 of the samples, the members among them in descending order
+    constexpr int STEP = ITEMS / 16;
+    uint32_t key[16];
+    int32_t none[16];
+    uint32_t m = 0u;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float x = v[i * STEP];
+      key[i] = member(x) ? desc_key(x + 0.0f) : 0xffffffffu;   // (one zero)
+      m += member(x) ? 1u : 0u;
+    }
+    m = wave_sum(m);
+    __syncthreads();
+    if (lane == 0) crowd[0][wid] = m;
+    __syncthreads();
+    m = 0u;
+#pragma unroll
+    for (int i = 0; i < W; ++i) m += crowd[0][i];
+    block_sort_u32<WT, 16, false>(key, none, sorted, ssm);   // (leaves the order in `sorted`)
+    if (m > 0u) {
+      auto at = [&](int c) {
+        const uint32_t q = static_cast<uint32_t>(c) * m / (NC - 2);
+        return sorted[buf_at(static_cast<int>(q < m ? q : m - 1u))];
+      };
+      // of equal bounds the last is the value, those before it the next
+      // float above: one cell of that value alone, the others empty
+      if (tid < NC - 1) {
+        const uint32_t key0 = at(tid);
+        const bool again = tid < NC - 2 && at(tid + 1) == key0;
+        bounds[static_cast<int64_t>(blockIdx.y) * NC + tid] = key_float(key0 - (again ? 1u : 0u));
+      }
+      w.scale = -1.0f;
+    }
+  }
+  if (tid == 0) win[blockIdx.y] = w;
 }
 
 // ------------------------------------------------------------------ pass ---
@@ -357,7 +459,7 @@ __global__ __launch_bounds__(LT) void long_pass_kernel(const float* __restrict__
     cu[e] = 0ull;
     cd[e] = 0ull;
   }
-  for (int e = tid; e <= NC; e += LT) edge[e] = edge_of<NC>(w, e);
+  for (int e = tid; e <= NC; e += LT) edge[e] = edge_of<NC>(w, o.bound + row * NC, e);
   const double xhi = w.xhi, xlo = w.xlo;
   const float farf = static_cast<float>(fmin(fmax(150.0 / c2, 1e-37), 3.0e38));   // beyond: 2^-150, no part of the sums
   double TR = 0.0, TL = 0.0;
@@ -466,7 +568,7 @@ __global__ __launch_bounds__(LT) void long_pass_kernel(const float* __restrict__
     D = __double2ull_rn(exp2_neg(fmin(edge[c + 1] - vd, 0.0) * c2) * fscale);
   };
   auto add = [&](float v, int c, uint32_t cnt, unsigned long long U, unsigned long long D) {
-    const uint32_t key = desc_key(v);
+    const uint32_t key = desc_key(v + 0.0f);   // (one zero)
     atomicMin(&kmin[c], key);
     atomicMax(&kmax[c], key);
     if (U) atomicAdd(&cu[c], U * cnt);
@@ -485,7 +587,7 @@ __global__ __launch_bounds__(LT) void long_pass_kernel(const float* __restrict__
         const int at = i * kWave + lane;
         if (at < staged) {
           mv[i] = stage[wid][at];
-          mc[i] = cell_of<NC>(w, mv[i]);
+          mc[i] = cell_at<NC>(w, edge, mv[i]);
           unsigned long long U, D;
           terms(mv[i], mc[i], U, D);
           mr[i] = add(mv[i], mc[i], 1u, U, D);
@@ -504,7 +606,7 @@ __global__ __launch_bounds__(LT) void long_pass_kernel(const float* __restrict__
         const float v0 = readlane_as(v, __ffsll(static_cast<long long>(m)) - 1);
         const uint64_t eq = __ballot(in && v == v0);
         if (lane == __ffsll(static_cast<long long>(m)) - 1) {
-          const int c = cell_of<NC>(w, v);
+          const int c = cell_at<NC>(w, edge, v);
           unsigned long long U, D;
           terms(v, c, U, D);
           add(v, c, static_cast<uint32_t>(__popcll(eq)), U, D);
@@ -512,7 +614,7 @@ __global__ __launch_bounds__(LT) void long_pass_kernel(const float* __restrict__
         in = in && v != v0;
       }
       if (in) {
-        const int c = cell_of<NC>(w, v);
+        const int c = cell_at<NC>(w, edge, v);
         unsigned long long U, D;
         terms(v, c, U, D);
         add(v, c, 1u, U, D);
@@ -522,7 +624,6 @@ __global__ __launch_bounds__(LT) void long_pass_kernel(const float* __restrict__
   __syncthreads();
   const int64_t slot = row * G + g;
   // entries per cell (one for equal members), their offsets, and the cells
-  // (+0 and -0 differ as keys, so a cell of both is written in full)
   if (wid == 0) {
     uint32_t run = 0u;
     uint32_t merged = 0u;
@@ -574,7 +675,7 @@ __global__ __launch_bounds__(LT) void long_pass_kernel(const float* __restrict__
     for (int64_t at = c0 + tid; at < c1; at += LT) {
       const float v = r[at];
       if (v < w.xhi && v >= w.xlo) {
-        const int c = cell_of<NC>(w, v);
+        const int c = cell_at<NC>(w, edge, v);
         if (!single(c)) list[atomicAdd(&cur[c], 1u)] = v;
       }
     }
@@ -634,18 +735,252 @@ __global__ __launch_bounds__(256) void long_merge_kernel(int G, LongCells o) {
 }
 
 // ------------------------------------------------------------------ root ---
+namespace {
+// LapSum at every edge of NC cells (cn members each, the two sums U and D):
+// P, the scores above an edge, and T, those below, move from edge to edge by
+// the cells' links e^{-(edge(c) - edge(c+1))/t} (affine scans over the lanes of
+// one wave, NC / 64 cells each).  above, TR, TL: the scores above the cells
+// and the sums at their two ends.  ab[c]: members in the cells before c.
+template <int NC>
+__device__ void edge_sums(const uint32_t* cn, const double* U, const double* D, const double* edge,
+                          double above, double TR, double TL, double c2, uint32_t* ab, double* eP,
+                          double* eT, double* lap) {
+  const int lane = lane_id();
+  uint32_t run = 0u;
+#pragma unroll
+  for (int q = 0; q < NC / kWave; ++q) {
+    const uint32_t v = cn[q * kWave + lane];
+    const uint32_t incl = wave_incl_add<uint32_t>(v);
+    ab[q * kWave + lane] = run + incl - v;
+    run += readlane_as(incl, kWave - 1);
+  }
+  if (lane == 0) ab[NC] = run;
+  constexpr int PER = NC / kWave;
+  const int c0 = PER * lane;
+  double lk[PER], T[PER + 1];
+  double Au = 1.0, Bu = 0.0, Ad = 1.0, Bd = 0.0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    lk[q] = exp2_neg(fmin(edge[c0 + q + 1] - edge[c0 + q], 0.0) * c2);
+    Bu = fma(lk[q], Bu, D[c0 + q]);
+    Au *= lk[q];
+  }
+#pragma unroll
+  for (int q = PER - 1; q >= 0; --q) Bd = fma(lk[q], Bd, U[c0 + q]);
+  Ad = Au;
+  wave_affine_up(Au, Bu);
+  wave_affine_down(Ad, Bd);
+  double P = __shfl_up(fma(Au, TR, Bu), 1, kWave);
+  if (lane == 0) P = TR;
+  T[PER] = __shfl_down(fma(Ad, TL, Bd), 1, kWave);
+  if (lane == kWave - 1) T[PER] = TL;
+#pragma unroll
+  for (int q = PER - 1; q >= 0; --q) T[q] = fma(lk[q], T[q + 1], U[c0 + q]);
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    eP[c0 + q] = P;
+    eT[c0 + q] = T[q];
+    lap[c0 + q] = above + static_cast<double>(ab[c0 + q]) - 0.5 * P + 0.5 * T[q];
+    P = fma(lk[q], P, D[c0 + q]);
+  }
+  if (lane == kWave - 1) {
+    eP[NC] = P;
+    eT[NC] = TL;
+    lap[NC] = above + static_cast<double>(ab[NC]) - 0.5 * P + 0.5 * TL;
+  }
+}
+
+// js[0]: the cell holding b, the last one whose upper edge has LapSum <= k
+// (cell 0 when none has); js[1], js[2]: its nearest non-empty neighbours.  One
+// wave.
+template <int NC>
+__device__ void root_cell(const uint32_t* cn, const double* lap, double k, int* js) {
+  const int lane = lane_id();
+  int js_ = 0;
+#pragma unroll
+  for (int q = 0; q < NC / kWave; ++q) {
+    const int c = q * kWave + lane;
+    if (c > 0 && lap[c] <= k) js_ = c;
+  }
+  js_ = static_cast<int>(wave_max_u32(static_cast<uint32_t>(js_)));
+  uint32_t jp = 0u, jn = NC - 1;   // (the last cell kept if none is non-empty)
+#pragma unroll
+  for (int q = 0; q < NC / kWave; ++q) {
+    const int c = q * kWave + lane;
+    if (cn[c] != 0u && c < js_) jp = static_cast<uint32_t>(c);
+    if (cn[NC - 1 - c] != 0u && NC - 1 - c > js_) jn = static_cast<uint32_t>(NC - 1 - c);
+  }
+  jp = wave_max_u32(jp);
+  jn = wave_min_u32(jn);
+  if (lane == 0) {
+    js[0] = js_;
+    js[1] = static_cast<int>(jp);
+    js[2] = static_cast<int>(jn);
+  }
+}
+
+// More entries than LDS holds (each(f) over all of them): 256 cells by a
+// sample of the row's scores in their range, one pass over the entries for the
+// cells' sums, one to collect those of the root's cell and its neighbours in
+// LDS.  A cell of equal entries is collected as one.  Two passes of 16 waves
+// instead of one of four waves for each of 10 to 20 points.  (The sample is
+// the row's and not the entries', whose order in a list is not always the
+// same: every call takes the same cells.)
+constexpr int kSub = 256;
+constexpr int kSubCap = 8192;   // entries collected, then their weights
+struct SubCells {
+  uint32_t cn[kSub], en[kSub], kmin[kSub], kmax[kSub], ab[kSub + 1];
+  uint32_t fill;
+  unsigned long long cu[kSub], cd[kSub];
+  double U[kSub], D[kSub], edge[kSub + 1], lap[kSub + 1], eP[kSub + 1], eT[kSub + 1];
+};
+static_assert(4 * (2 * kSubCap) + sizeof(SubCells) <= 4 * kRootCap, "the cells lie behind the entries");
+static_assert(sort_buf_words<MT, 4>() <= kSubCap && sizeof(SortSmem<MT>) <= 4 * kSubCap, "sample");
+
+// What is narrowed: `count` entries of the total weight, the scores outside
+// them as carries, and the first point.
+struct Crowd {
+  uint32_t count, weight;
+  Carry ext;
+  float x0;
+};
+
+// top, bottom: the entries' range (infinite: open).  buf: kRootCap words;
+// true: the entries are in buf[0 .. count), their weights kSubCap words behind
+// them, and q says the rest; false (too many left): nothing has changed.
+template <int BT, class Each>
+__device__ bool divide_crowd(Each&& each, const float* __restrict__ r, int64_t n, double top,
+                             double bottom, double k, double t, float* buf, int* js, Crowd& q) {
+  constexpr int M = 4096;   // scores sampled, at most
+  constexpr int SI = M / BT;
+  uint32_t* sorted = reinterpret_cast<uint32_t*>(buf);
+  SortSmem<BT>& ssm = *reinterpret_cast<SortSmem<BT>*>(buf + kSubCap);
+  SubCells& S = *reinterpret_cast<SubCells*>(buf + 2 * kSubCap);
+  const int tid = threadIdx.x;
+  const double c2 = kLog2e / t;
+  // 1. the cells' bounds: hashed positions of the row, up to 65536 of them or
+  //    until 3072 scores in the range have been met, in order
+  for (int c = tid; c < kSub; c += BT) {
+    S.cn[c] = S.en[c] = 0u;
+    S.kmin[c] = 0xffffffffu;
+    S.kmax[c] = 0u;
+    S.cu[c] = S.cd[c] = 0ull;
+  }
+  if (tid == 0) S.fill = 0u;
+  __syncthreads();
+  int m = 0;
+  for (int i = 0; i < 64 && m <= M - BT; ++i) {
+    const uint64_t h = mix32(static_cast<uint32_t>(i * BT + tid) + 0x51ed2700u);
+    const float x = fminf(fmaxf(r[(h * static_cast<uint64_t>(n)) >> 32], -kMaxScore), kMaxScore);
+    const bool in = x < top && x >= bottom;   // (so that no bound lies above top)
+    const uint64_t b = __ballot(in);
+    uint32_t at = 0u;
+    if (lane_id() == 0) at = atomicAdd(&S.fill, static_cast<uint32_t>(__popcll(b)));
+    at = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(at)));
+    if (in) sorted[at + __popcll(b & ((1ull << lane_id()) - 1ull))] = desc_key(x + 0.0f);
+    __syncthreads();
+    m = static_cast<int>(S.fill);
+    __syncthreads();
+  }
+  if (m == 0) return false;
+  {
+    uint32_t key[SI];
+    int32_t none[SI];
+#pragma unroll
+    for (int i = 0; i < SI; ++i) key[i] = i * BT + tid < m ? sorted[i * BT + tid] : 0xffffffffu;
+    if (tid == 0) S.fill = 0u;
+    block_sort_u32<BT, SI, false>(key, none, sorted, ssm);   // (leaves the order in `sorted`)
+  }
+  for (int c = tid; c < kSub - 1; c += BT) {
+    auto key_at = [&](int b) {
+      const int i = b * m / (kSub - 2);
+      return sorted[buf_at(i < m ? i : m - 1)];
+    };
+    const uint32_t key0 = key_at(c);
+    const bool again = c < kSub - 2 && key_at(c + 1) == key0;   // (as in long_window)
+    const double e = key_float(key0 - (again ? 1u : 0u));
+    S.edge[c + 1] = e;
+    // (an open end: the sample's own last score)
+    if (c == 0) S.edge[0] = top < INFINITY ? fmax(e, top) : e;
+    if (c == kSub - 2) S.edge[kSub] = bottom > -INFINITY ? fmin(e, bottom) : e;
+  }
+  __syncthreads();
+  auto cell = [&](float v) { return cell_by_edges<kSub>(S.edge, v); };
+  // 2. their sums, in fixed point
+  const int fbits = 62 - (64 - __clzll(static_cast<long long>(q.weight) | 1ll));
+  const double fscale = ldexp(1.0, fbits), inv_f = ldexp(1.0, -fbits);
+  each([&](float v, uint32_t w) {
+    const int c = cell(v);
+    const double vd = v;
+    const unsigned long long U = __double2ull_rn(exp2_neg(fmin(vd - S.edge[c], 0.0) * c2) * fscale);
+    const unsigned long long D = __double2ull_rn(exp2_neg(fmin(S.edge[c + 1] - vd, 0.0) * c2) * fscale);
+    const uint32_t kv = desc_key(v + 0.0f);
+    atomicMin(&S.kmin[c], kv);
+    atomicMax(&S.kmax[c], kv);
+    atomicAdd(&S.cu[c], U * w);
+    atomicAdd(&S.cd[c], D * w);
+    atomicAdd(&S.cn[c], w);
+    atomicAdd(&S.en[c], 1u);
+  });
+  __syncthreads();
+  for (int c = tid; c < kSub; c += BT) {
+    S.U[c] = static_cast<double>(S.cu[c]) * inv_f;
+    S.D[c] = static_cast<double>(S.cd[c]) * inv_f;
+  }
+  __syncthreads();
+  if (tid < kWave) {
+    const Carry& x = q.ext;
+    const double TR = x.pre.S * exp2_neg(fmin(S.edge[0] - static_cast<double>(x.pre.u), 0.0) * c2);
+    const double TL = x.suf.T * exp2_neg(fmin(static_cast<double>(x.suf.v) - S.edge[kSub], 0.0) * c2);
+    edge_sums<kSub>(S.cn, S.U, S.D, S.edge, x.rank0, TR, TL, c2, S.ab, S.eP, S.eT, S.lap);
+    root_cell<kSub>(S.cn, S.lap, k, js);
+  }
+  __syncthreads();
+  const int j = js[0], jp = js[1], jn = js[2];
+  auto single = [&](int c) { return S.en[c] > 1u && S.kmin[c] == S.kmax[c]; };
+  auto left_of = [&](int c) { return single(c) ? 1u : S.en[c]; };
+  // (only these three of the cells jp .. jn hold entries)
+  const uint32_t left = left_of(j) + (jp != j ? left_of(jp) : 0u) + (jn != j && jn != jp ? left_of(jn) : 0u);
+  if (left > static_cast<uint32_t>(kSubCap)) return false;
+  // 3. the entries of cells jp .. jn, everything else as carries
+  uint32_t* bw = reinterpret_cast<uint32_t*>(buf) + kSubCap;
+  auto keep = [&](float v, uint32_t w) {
+    const uint32_t e = atomicAdd(&S.fill, 1u);
+    if (e < static_cast<uint32_t>(kSubCap)) {
+      buf[e] = v;
+      bw[e] = w;
+    }
+  };
+  each([&](float v, uint32_t w) {
+    const int c = cell(v);
+    if (c >= jp && c <= jn && !single(c)) keep(v, w);
+  });
+  for (int c = jp + tid; c <= jn; c += BT)
+    if (single(c)) keep(key_float(S.kmin[c]), S.cn[c]);
+  q.ext.rank0 += static_cast<double>(S.ab[jp]);
+  if (jp > 0)
+    q.ext.pre = S.eP[jp] > 0.0 ? Pre{static_cast<float>(S.edge[jp]), S.eP[jp]} : pre_empty();
+  if (jn < kSub - 1)
+    q.ext.suf = S.eT[jn + 1] > 0.0 ? Suf{static_cast<float>(S.edge[jn + 1]), S.eT[jn + 1]} : suf_empty();
+  q.weight = S.ab[jn + 1] - S.ab[jp];
+  q.x0 = static_cast<float>(0.5 * (S.edge[j] + S.edge[j + 1]));
+  q.count = left;
+  __syncthreads();
+  return true;
+}
+}  // namespace
+
 // MERGED: long_merge has run.
 template <int NC, bool MERGED>
-__global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
+__global__ __launch_bounds__(MT) void long_root_kernel(
     const float* __restrict__ scores, int64_t n, int64_t chunk, int G, double k, double t,
     LongCells o, double* __restrict__ b_out) {
   constexpr int W = WT / kWave;
-  constexpr int T0 = MERGED ? WT : MT;
+  constexpr int T0 = MT;
   constexpr int GR = MERGED ? 1 : MT / NC;   // groups of threads, each merging every GR-th block
   static_assert(NC <= WT && WT % NC == 0, "cells are spread over the threads");
   __shared__ NarrowSmem<WT> nsm;
-  __shared__ float lv[kRootCap];
-  uint32_t* lw = reinterpret_cast<uint32_t*>(lv) + kRootCap / 2;   // with merged cells
+  __shared__ __align__(16) float lv[kRootCap];
   __shared__ double pU[GR][NC], pD[GR][NC];
   __shared__ uint32_t pc[GR][NC];
   __shared__ double U[NC], D[NC];
@@ -666,7 +1001,7 @@ __global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
   const int64_t s0 = row * G;
   const double c2 = kLog2e / t;
   // 1. tails and cells over the blocks, in a fixed order
-  for (int e = tid; e <= NC; e += T0) edge[e] = edge_of<NC>(w, e);
+  for (int e = tid; e <= NC; e += T0) edge[e] = edge_of<NC>(w, o.bound + row * NC, e);
   if (tid < WT) {
     double TR = 0.0, TL = 0.0;
     uint32_t nR = 0u, m = 0u;
@@ -727,8 +1062,6 @@ __global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
     pD[gi][c] = sd;
     pc[gi][c] = sc;
     __syncthreads();
-    if (wid >= W) return;   // one wave per SIMD from here on (ended waves
-                            // take no part in the barriers below)
     if (tid < NC) {
       su = sd = 0.0;
       sc = 0u;
@@ -744,17 +1077,6 @@ __global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
     }
     __syncthreads();
   }
-  if (wid == 0) {
-    uint32_t run = 0u;
-#pragma unroll
-    for (int q = 0; q < NC / kWave; ++q) {
-      const uint32_t v = cn[q * kWave + lane];
-      const uint32_t incl = wave_incl_add<uint32_t>(v);
-      ab[q * kWave + lane] = run + incl - v;
-      run += readlane_as(incl, kWave - 1);
-    }
-    if (lane == 0) ab[NC] = run;
-  }
   double TR = 0.0, TL = 0.0;
   uint32_t nR = 0u, merged = 0u;
 #pragma unroll
@@ -765,80 +1087,21 @@ __global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
     merged |= mg[i];
   }
   const bool bounded_hi = w.xhi < INFINITY, bounded_lo = w.xlo > -INFINITY;
-  // 2. LapSum at every edge: P, the scores above an edge, and T, those below,
-  //    move from edge to edge by the cells' links e^{-(edge(c) - edge(c+1))/t}
-  //    (affine scans over the lanes of one wave, NC / 64 cells each)
+  // 2. LapSum at every edge, and the cell holding b with its neighbours
   if (wid == 0) {
-    constexpr int PER = NC / kWave;
-    const int c0 = PER * lane;
-    double lk[PER], T[PER + 1];
-    double Au = 1.0, Bu = 0.0, Ad = 1.0, Bd = 0.0;
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      lk[q] = exp2_neg(fmin(edge[c0 + q + 1] - edge[c0 + q], 0.0) * c2);
-      Bu = fma(lk[q], Bu, D[c0 + q]);
-      Au *= lk[q];
-    }
-#pragma unroll
-    for (int q = PER - 1; q >= 0; --q) Bd = fma(lk[q], Bd, U[c0 + q]);
-    Ad = Au;
-    wave_affine_up(Au, Bu);
-    wave_affine_down(Ad, Bd);
-    double P = __shfl_up(fma(Au, TR, Bu), 1, kWave);
-    if (lane == 0) P = TR;
-    T[PER] = __shfl_down(fma(Ad, TL, Bd), 1, kWave);
-    if (lane == kWave - 1) T[PER] = TL;
-#pragma unroll
-    for (int q = PER - 1; q >= 0; --q) T[q] = fma(lk[q], T[q + 1], U[c0 + q]);
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      eP[c0 + q] = P;
-      eT[c0 + q] = T[q];
-      lap[c0 + q] = static_cast<double>(nR) + static_cast<double>(ab[c0 + q]) - 0.5 * P + 0.5 * T[q];
-      P = fma(lk[q], P, D[c0 + q]);
-    }
-    if (lane == kWave - 1) {
-      eP[NC] = P;
-      eT[NC] = TL;
-      lap[NC] = static_cast<double>(nR) + static_cast<double>(ab[NC]) - 0.5 * P + 0.5 * TL;
-    }
-  }
-  __syncthreads();
-  // 3. the cell holding b: the last one whose upper edge has LapSum <= k
-  //    (cell 0 when none has), with its nearest non-empty neighbours
-  if (wid == 0) {
-    int js_ = 0;
-#pragma unroll
-    for (int q = 0; q < NC / kWave; ++q) {
-      const int c = q * kWave + lane;
-      if (c > 0 && lap[c] <= k) js_ = c;
-    }
-    js_ = static_cast<int>(wave_max_u32(static_cast<uint32_t>(js_)));
-    uint32_t jp = 0u, jn = NC - 1;   // (the last cell kept if none is non-empty)
-#pragma unroll
-    for (int q = 0; q < NC / kWave; ++q) {
-      const int c = q * kWave + lane;
-      if (cn[c] != 0u && c < js_) jp = static_cast<uint32_t>(c);
-      if (cn[NC - 1 - c] != 0u && NC - 1 - c > js_) jn = static_cast<uint32_t>(NC - 1 - c);
-    }
-    jp = wave_max_u32(jp);
-    jn = wave_min_u32(jn);
-    if (lane == 0) {
-      js[0] = js_;
-      js[1] = static_cast<int>(jp);
-      js[2] = static_cast<int>(jn);
-    }
+    edge_sums<NC>(cn, U, D, edge, nR, TR, TL, c2, ab, eP, eT, lap);
+    root_cell<NC>(cn, lap, k, js);
   }
   __syncthreads();
   const int jp = js[1], jn = js[2];
   const bool direct = !(bounded_hi && lap[0] > k) && !(bounded_lo && lap[NC] < k);
-  // 4. carries: everything above cell jp and below cell jn (at cell 0 and
+  // 3. carries: everything above cell jp and below cell jn (at cell 0 and
   //    cell NC-1 the edge is the window's own end)
   Carry ext;
   ext.rank0 = static_cast<double>(nR) + static_cast<double>(ab[jp]);
   ext.pre = eP[jp] > 0.0 ? Pre{static_cast<float>(edge[jp]), eP[jp]} : pre_empty();
   ext.suf = eT[jn + 1] > 0.0 ? Suf{static_cast<float>(edge[jn + 1]), eT[jn + 1]} : suf_empty();
-  // 5. the entries of cells jp .. jn of every block
+  // 4. the entries of cells jp .. jn of every block
   {
     constexpr int PB = kLongMaxBlocks / WT;   // consecutive blocks per thread
     uint32_t mine[PB], loc = 0u;
@@ -846,7 +1109,7 @@ __global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
     for (int q = 0; q < PB; ++q) {
       const int bb = tid * PB + q;
       mine[q] = 0u;
-      if (bb < G) {
+      if (tid < WT && bb < G) {
         const uint32_t first = o.off[(s0 + bb) * (NC + 1) + jp];
         mine[q] = o.off[(s0 + bb) * (NC + 1) + jn + 1] - first;
         at_n[bb] = (s0 + bb) * chunk + first;
@@ -854,76 +1117,105 @@ __global__ __launch_bounds__(MERGED ? WT : MT) void long_root_kernel(
       loc += mine[q];
     }
     const uint32_t incl = wave_incl_add<uint32_t>(loc);
-    if (lane == kWave - 1) wt[wid] = incl;
+    if (lane == kWave - 1 && wid < W) wt[wid] = incl;
     __syncthreads();
     uint32_t run = incl - loc;
 #pragma unroll
     for (int i = 0; i < W; ++i)
       if (i < wid) run += wt[i];
+    if (tid < WT) {
 #pragma unroll
-    for (int q = 0; q < PB; ++q) {
-      pre_n[tid * PB + q] = run;   // blocks past G hold the total
-      run += mine[q];
+      for (int q = 0; q < PB; ++q) {
+        pre_n[tid * PB + q] = run;   // blocks past G hold the total
+        run += mine[q];
+      }
     }
     if (tid == WT - 1) pre_n[kLongMaxBlocks] = run;
   }
   __syncthreads();
   const uint32_t total = pre_n[kLongMaxBlocks];
-  // the weight of an entry of block bb (a merged cell stands for its count)
+  // entry e of them: its block, its score, and its weight (a merged cell
+  // stands for its count)
+  auto block_of = [&](uint32_t e) {
+    int lo = 0;   // the last with pre_n[lo] <= e (blocks past G hold the total)
+#pragma unroll
+    for (int step = kLongMaxBlocks / 2; step > 0; step >>= 1) lo += pre_n[lo + step] <= e ? step : 0;
+    return lo;
+  };
+  auto entry = [&](int bb, uint32_t e) { return o.list[at_n[bb] + (e - pre_n[bb])]; };
   auto weight_of = [&](int bb, float x) -> uint32_t {
-    const int c = cell_of<NC>(w, x);
+    const int c = cell_at<NC>(w, edge, x);
     const uint32_t* off = o.off + (s0 + bb) * (NC + 1);
     return off[c + 1] - off[c] == 1u ? o.cnt[(s0 + bb) * NC + c] : 1u;
   };
-  // from the middle of the cell
-  const float x0 = static_cast<float>(0.5 * (edge[js[0]] + edge[js[0] + 1]));
-  const uint32_t weight = ab[jn + 1] - ab[jp];
   double b;
   if (direct && total <= static_cast<uint32_t>(merged ? kRootCap / 2 : kRootCap)) {
+    if (wid >= W) return;   // one wave per SIMD from here on (ended waves
+                            // take no part in the barriers below)
+    uint32_t* lw = reinterpret_cast<uint32_t*>(lv) + kRootCap / 2;   // with merged cells
 #pragma unroll 2
     for (uint32_t e = tid; e < total; e += WT) {
-      int lo = 0, hi = G;   // pre_n[lo] <= e < pre_n[hi]
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (pre_n[mid] <= e) lo = mid; else hi = mid;
-      }
-      const float x = o.list[at_n[lo] + (e - pre_n[lo])];
+      const int bb = block_of(e);
+      const float x = entry(bb, e);
       lv[e] = x;
-      if (merged) lw[e] = weight_of(lo, x);
+      if (merged) lw[e] = weight_of(bb, x);
     }
     // (each thread reads back only what it wrote)
     auto each = [&](auto&& f) {
       for (uint32_t e = tid; e < total; e += WT) f(lv[e], merged ? lw[e] : 1u);
     };
-    b = narrow_solve<WT>(each, total, weight, ext, -INFINITY, INFINITY, x0, k, t, nsm);
-  } else if (direct) {
-    // more entries than LDS holds: straight from the blocks' lists, a wave
-    // per block
+    // (from the middle of the cell)
+    const float x0 = static_cast<float>(0.5 * (edge[js[0]] + edge[js[0] + 1]));
+    b = narrow_solve<WT>(each, total, ab[jn + 1] - ab[jp], ext, -INFINITY, INFINITY, x0, k, t, nsm);
+  } else {
+    // more entries than LDS holds, in the blocks' lists, or a root outside the
+    // window, anywhere in the row
+    enum { kOnChip, kLists, kRow };
+    int from = direct ? kLists : kRow;
+    int T = T0;   // threads that take part
+    Crowd q;
+    q.count = direct ? total : static_cast<uint32_t>(n);
+    q.weight = direct ? ab[jn + 1] - ab[jp] : static_cast<uint32_t>(n);
+    q.ext = direct ? ext : Carry{0.0, pre_empty(), suf_empty()};
+    q.x0 = direct ? static_cast<float>(0.5 * (edge[js[0]] + edge[js[0] + 1])) : w.x0;
     auto each = [&](auto&& f) {
-      for (int bb = wid; bb < G; bb += W) {
-        const uint32_t cnt = pre_n[bb + 1] - pre_n[bb];
-        for (uint32_t e = lane; e < cnt; e += kWave) {
-          const float x = o.list[at_n[bb] + e];
-          f(x, merged ? weight_of(bb, x) : 1u);
+      if (from == kOnChip) {
+        const uint32_t* lw = reinterpret_cast<const uint32_t*>(lv) + kSubCap;
+        for (uint32_t e = tid; e < q.count; e += T) f(lv[e], lw[e]);
+      } else if (from == kLists) {
+        for (uint32_t e0 = 0u; e0 < total; e0 += 4 * T) {
+          float x[4];
+          uint32_t xw[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const uint32_t e = e0 + i * T + tid;
+            const uint32_t ee = e < total ? e : 0u;
+            const int bb = block_of(ee);
+            x[i] = entry(bb, ee);
+            xw[i] = merged ? weight_of(bb, x[i]) : 1u;
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (e0 + i * T + tid < total) f(x[i], xw[i]);
+        }
+      } else {
+        for (int64_t i0 = 0; i0 < n; i0 += 4 * T) {
+          float x[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x[i] = r[i0 + i * T + tid < n ? i0 + i * T + tid : 0];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (i0 + i * T + tid < n) f(x[i], 1u);
         }
       }
     };
-    b = narrow_solve<WT>(each, total, weight, ext, -INFINITY, INFINITY, x0, k, t, nsm);
-  } else {
-    auto each = [&](auto&& f) {
-      int64_t i = tid;
-      for (; i + 3 * WT < n; i += 4 * WT) {
-        float v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = r[i + q * WT];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) f(v[q], 1u);
-      }
-      for (; i < n; i += WT) f(r[i], 1u);
-    };
-    const Carry none{0.0, pre_empty(), suf_empty()};
-    b = narrow_solve<WT>(each, static_cast<uint32_t>(n), static_cast<uint32_t>(n), none, -INFINITY,
-                         INFINITY, w.x0, k, t, nsm);
+    // (a first or last cell that is not bounded has no end)
+    const double top = direct && (jp > 0 || bounded_hi) ? edge[jp] : INFINITY;
+    const double bottom = direct && (jn < NC - 1 || bounded_lo) ? edge[jn + 1] : -INFINITY;
+    if (divide_crowd<T0>(each, r, n, top, bottom, k, t, lv, js, q)) from = kOnChip;
+    if (wid >= W) return;
+    T = WT;
+    b = narrow_solve<WT>(each, q.count, q.weight, q.ext, -INFINITY, INFINITY, q.x0, k, t, nsm);
   }
   if (tid == 0) b_out[row] = b;
 }
@@ -970,6 +1262,7 @@ LongCells long_view(void* ws, int64_t rows, const LongGrid& lg, int64_t n, size_
   size_t off = 0;
   LongCells o;
   o.win = carve<Window>(base, off, static_cast<size_t>(rows));
+  o.bound = carve<float>(base, off, static_cast<size_t>(rows) * NC);
   o.mU = carve<double>(base, off, static_cast<size_t>(rows) * NC);
   o.mD = carve<double>(base, off, static_cast<size_t>(rows) * NC);
   o.mcnt = carve<uint32_t>(base, off, static_cast<size_t>(rows) * NC);
@@ -1016,11 +1309,14 @@ hipError_t launch_long_solve(const float* scores, int64_t rows, int64_t group, i
   const bool wide = long_wide(n);
   { ProfScope ps_("long_window", s);
   if (n > (int64_t(1) << 24))
-    hipLaunchKernelGGL((long_window_kernel<64, 256>), dim3(1, ry), dim3(WT), 0, s, scores, n, k, t, o.win);
+    hipLaunchKernelGGL((long_window_kernel<64, 256>), dim3(1, ry), dim3(WT), 0, s, scores, n, k, t, o.win,
+                       o.bound);
   else if (wide)
-    hipLaunchKernelGGL((long_window_kernel<16, 256>), dim3(1, ry), dim3(WT), 0, s, scores, n, k, t, o.win);
+    hipLaunchKernelGGL((long_window_kernel<16, 256>), dim3(1, ry), dim3(WT), 0, s, scores, n, k, t, o.win,
+                       o.bound);
   else
-    hipLaunchKernelGGL((long_window_kernel<16, 64>), dim3(1, ry), dim3(WT), 0, s, scores, n, k, t, o.win); }
+    hipLaunchKernelGGL((long_window_kernel<16, 64>), dim3(1, ry), dim3(WT), 0, s, scores, n, k, t, o.win,
+                       o.bound); }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   { ProfScope ps_("long_pass", s);
@@ -1039,7 +1335,7 @@ hipError_t launch_long_solve(const float* scores, int64_t rows, int64_t group, i
   }
   { ProfScope ps_("long_root", s);
   if (wide)
-    hipLaunchKernelGGL((long_root_kernel<256, true>), dim3(1, ry), dim3(WT), 0, s, scores, n,
+    hipLaunchKernelGGL((long_root_kernel<256, true>), dim3(1, ry), dim3(MT), 0, s, scores, n,
                        lg.chunk, lg.G, k, t, o, b);
   else
     hipLaunchKernelGGL((long_root_kernel<64, false>), dim3(1, ry), dim3(MT), 0, s, scores, n,

@@ -85,8 +85,10 @@ __device__ double narrow_solve(Each&& each, uint32_t total, uint32_t weight, con
   uint32_t left = total;
   float x = x0;
   int same = 0, last = 0;
+  bool key = false;   // the last point was a middle of the keys
   // LapSum at the ends (about, until they are points)
   double flo = ext.rank0 + static_cast<double>(weight), fhi = ext.rank0;
+  const double noise = 1e-14 * flo;
   // the set's range, where the middle of an end still open is taken
   float mn = INFINITY, mx = -INFINITY;
   if (left > static_cast<uint32_t>(kNarrowMax)) {
@@ -148,8 +150,11 @@ __device__ double narrow_solve(Each&& each, uint32_t total, uint32_t weight, con
     P += ext.pre.S * exp2_neg(fmin(xd - static_cast<double>(ext.pre.u), 0.0) * c2);
     E += ext.suf.T * exp2_neg(fmin(static_cast<double>(ext.suf.v) - xd, 0.0) * c2);
     const double f = ext.rank0 + static_cast<double>(c) - 0.5 * P + 0.5 * E;
+    const uint32_t old = left;
     int side;
-    if (f <= k) {
+    // (LapSum within its sums' rounding of the budget counts as equal to it, so
+    // that their order does not decide where LapSum is flat around the root)
+    if (f - k <= noise) {
       hi = x;
       fhi = f;
       left = na;
@@ -168,7 +173,7 @@ __device__ double narrow_solve(Each&& each, uint32_t total, uint32_t weight, con
     // the ends in proportion to LapSum, every second time their middle
     float xn = x;
     const double F = 0.5 * (P + E);
-    if (it < 12 && F > 0.0) {
+    if (it < 12 && F > 0.0 && fabs(f - k) > noise) {
       const double step = t * (f - k) / F * static_cast<double>(1 << (same < 6 ? same : 6));
       xn = static_cast<float>(xd + step);
     }
@@ -178,6 +183,12 @@ __device__ double narrow_solve(Each&& each, uint32_t total, uint32_t weight, con
       xn = l + (h - l) * fminf(fmaxf(q, 0.05f), 0.95f);
     }
     if (!(xn > lo && xn < hi)) xn = middle(fmaxf(lo, mn), fminf(hi, mx), it);
+    // a set that spans many orders of magnitude (a sentinel, heavy tails): the
+    // middle of the keys after a point that left most of it between the ends
+    if (it >= 4) {
+      key = !key && left > old - old / 4u;
+      if (key) xn = key_mid(fmaxf(lo, mn), fminf(hi, mx));
+    }
     if (!(xn > lo && xn < hi)) xn = key_mid(lo, hi);
     x = xn;
     if (!(x > lo && x < hi)) break;   // no float between the ends

@@ -166,6 +166,65 @@ def test_masked_long_row(lib, n, share, low):
         assert ms <= 5.0 * ref, (n, share, low, k, ms, ref)
 
 
+def _check_equation(r, k, alpha, p, b, label):
+    """b against the budget equation itself, in extended precision over the
+    distinct scores: where scores are 1e7 temperatures from zero the oracle's
+    scan is 3e-8 t off (the kernel 3e-10 t), more than the bound on b."""
+    t, L = -alpha, np.longdouble
+    vals, cnt = np.unique(r, return_counts=True)
+    d = (vals.astype(L) - L(b)) / L(t)
+    e = 0.5 * np.exp(-np.abs(d))
+    res = np.sum(np.where(d >= 0, 1 - e, e) * cnt.astype(L)) - L(k)
+    slope = np.sum(e * cnt.astype(L)) / L(t)
+    assert abs(res) <= slope * L(2e-8 * t + 4e-16 * abs(b)), (label, b, float(res / slope))
+    assert float(np.max(np.abs(p.astype(np.float64) - O.probs(r, b, alpha)))) <= P_TOL, label
+    assert O.budget_error(p, k) <= sum_tol(k), label
+
+
+def _crowded(layout, n):
+    rng = np.random.default_rng([n, len(layout)])
+    x = rng.standard_normal(n)
+    u = rng.random(n)
+    if layout == "clusters":        # two, many temperatures apart
+        x = np.where(u < 0.5, 1000.0, -1000.0) + 1e-2 * x
+    elif layout == "zeros":         # one value among others close to it, of both signs
+        x = np.where(u < 0.6, np.where(u < 0.3, 0.0, -0.0), 0.3 * np.abs(x))
+    elif layout == "masked":        # a sentinel inside the window
+        x[u < 0.3] = LOWEST
+    elif layout == "few_masked":    # a sentinel below the last sampled score of the window
+        x[u < 0.01] = LOWEST
+    elif layout == "mixed":         # half of the row a thousand times narrower
+        x = np.where(u < 0.5, x, 1e-3 * x)
+    elif layout == "narrow":        # the whole row in the window
+        x = 1e-3 * x
+    elif layout == "offset":        # float32 steps as wide as a cell
+        x = 1000.0 + 1e-2 * x
+    return x.astype(np.float32)
+
+
+@pytest.mark.parametrize("n", [70_001, 262_144, 1_000_003, 6_000_000])
+@pytest.mark.parametrize("layout,kf,alpha", [
+    ("clusters", 0.5, -0.05), ("clusters", 0.2, -1e-4), ("zeros", 0.75, -0.05), ("zeros", 0.6, -1e-3),
+    ("masked", 0.69, -0.05), ("masked", 0.68, -1.0),
+    ("few_masked", 0.985, -0.05), ("mixed", 0.5, -0.05), ("mixed", 0.45, -1e-3), ("narrow", 0.5, -1.0),
+    ("offset", 0.5, -1e-3), ("offset", 0.3, -1e-4), ("offset", 0.02, -1e-3)])
+def test_long_row_with_crowded_cells(lib, n, layout, kf, alpha):
+    """Layouts that put most of a window's members into a few equal cells: the
+    cells follow the sample instead, and what is still too much for LDS is
+    divided (narrowed entry by entry they took up to 380 times a plain row's
+    time)."""
+    r = _crowded(layout, n)
+    x, plain = _t(r), _t(_crowded("plain", n))
+    k = kf * n
+    p, b = lib.lapsum_forward(x, k, alpha)
+    _check_equation(r, k, alpha, _np(p), float(_np(b)[0]), (n, layout, kf, alpha))
+    p2, b2 = lib.lapsum_forward(x, k, alpha)
+    assert np.array_equal(_np(b), _np(b2)) and np.array_equal(_np(p), _np(p2))
+    ms = _ms(lambda: lib.lapsum_forward(x, k, alpha))
+    ref = _ms(lambda: lib.lapsum_forward(plain, k, alpha))
+    assert ms <= 12.0 * ref, (n, layout, kf, alpha, ms, ref)
+
+
 def _sample_positions(n, m=4096):
     """Where the window's sample reads (one hashed position per stratum)."""
     s = np.arange(m, dtype=np.uint64)
@@ -179,12 +238,12 @@ def _sample_positions(n, m=4096):
     return (a + ((x.astype(np.uint64) * (e - a)) >> np.uint64(32))).astype(np.int64)
 
 
+@pytest.mark.parametrize("n", [50001, 1_500_001])
 @pytest.mark.parametrize("shift", [3.0, -3.0])
-def test_long_row_outside_its_window(lib, shift):
+def test_long_row_outside_its_window(lib, shift, n):
     """Scores laid out so that the sample sees another distribution than the
     row has: the root lies outside the window on either side, and the row is
-    narrowed whole."""
-    n = 50001
+    divided whole (past about 7e5 scores it is narrowed whole)."""
     rng = np.random.default_rng(17)
     r = rng.standard_normal(n).astype(np.float32)
     r[_sample_positions(n)] += np.float32(shift)
