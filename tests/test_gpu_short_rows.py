@@ -29,3 +29,35 @@ def test_short_rows_against_oracle(lib, n, batch):
                 assert abs(b[i] - ref) <= 2e-8 * -alpha + 4e-16 * abs(ref), (i, k, alpha)
                 err = np.max(np.abs(p[i].astype(np.float64) - O.probs(x[i], ref, alpha)))
                 assert err <= 2e-7, (i, k, alpha, err)
+
+
+@pytest.mark.parametrize("batch,n", [(4096, 200), (2048, 900)])
+@pytest.mark.parametrize("low", [float(np.finfo(np.float32).min), -1e30, -1e9])
+def test_masked_short_rows(lib, batch, n, low):
+    """Rows with a sentinel among the scores: right, and not much slower than
+    without (25 to 40 points a row by values, 9 to 15 with middles of the keys)."""
+    import torch
+    rng = np.random.default_rng([n, 3])
+    plain = rng.standard_normal((batch, n)).astype(np.float32)
+    x = np.where(rng.random(plain.shape) < 0.3, np.float32(low), plain)
+    xt, pt = _t(x), _t(plain)
+
+    def ms(t, k, alpha):
+        best = 1e9
+        for _ in range(8):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(5):
+                lib.lapsum_forward(t, k, alpha)
+            e1.record()
+            e1.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        return best
+    for k, alpha in ((0.05 * n, -1.0), (0.02 * n, -0.05), (0.4 * n, -0.2)):
+        p, b = lib.lapsum_forward(xt, k, alpha)
+        p, b = _np(p), _np(b)
+        for i in (0, 1, 2, batch - 1):
+            ref = O.solve_sorted_scan(x[i], k, alpha)
+            assert abs(b[i] - ref) <= 2e-8 * -alpha + 4e-16 * abs(ref), (i, k, alpha)
+            assert np.max(np.abs(p[i].astype(np.float64) - O.probs(x[i], ref, alpha))) <= 2e-7
+        assert ms(xt, k, alpha) <= 2.5 * ms(pt, k, alpha), (k, alpha)
