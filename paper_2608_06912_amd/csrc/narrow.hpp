@@ -83,7 +83,7 @@ __device__ double narrow_solve(Each&& each, uint32_t total, uint32_t weight, con
   const int wid = tid / kWave;
   const double c2 = kLog2e / t;
   uint32_t left = total;
-  float x = x0;
+  float x = x0 == x0 ? x0 : 0.0f;   // (a NaN point would end the search at once)
   int same = 0, last = 0;
   bool key = false;   // the last point was a middle of the keys
   // LapSum at the ends (about, until they are points)
@@ -274,7 +274,10 @@ __device__ double narrow_solve(Each&& each, uint32_t total, uint32_t weight, con
     suf = Suf{vm, s};
   }
   const double rank0 = ext.rank0 + static_cast<double>(cu);
-  const int ne = static_cast<int>(sm.fill < static_cast<uint32_t>(kNarrowMax) ? sm.fill : kNarrowMax);
+  // (the points end with at most kNarrowMax scores left, or with no float
+  // between the ends; anything else is no result)
+  if (sm.fill > static_cast<uint32_t>(kNarrowMax)) return NAN;
+  const int ne = static_cast<int>(sm.fill);
 
   // the scores left, in descending order (equal scores by weight): ranks by
   // counting, TPK adjacent threads to an entry
