@@ -27,7 +27,7 @@ import os
 
 import torch
 
-from . import (HERE, lapsum_backward, lapsum_backward_band, lapsum_bracket_noise,
+from . import (HERE, LapsumError, lapsum_backward, lapsum_backward_band, lapsum_bracket_noise,
                lapsum_forward, lapsum_forward_bracketed, lapsum_hard_mask, load, new_band)
 
 __all__ = ["soft_topk", "hard_topk_mask", "straight_through", "choose_path", "sample_size",
@@ -241,6 +241,19 @@ def hard_topk_mask(scores, k: int):
     return lapsum_hard_mask(x, int(k)).reshape(scores.shape)
 
 
+# Rows longer than this have always had their bracket options checked, also
+# where "auto" takes the full path, which has no use for them.
+_OPTIONS_MIN_N = 1 << 18
+
+
+def _check_bracket_options(sample, sampler, z):
+    sample_size(2, sample)
+    if sampler not in ("systematic", "iid"):
+        raise ValueError(f"unknown sampler {sampler!r}")
+    if not (math.isfinite(z) and z > 0.0):
+        raise LapsumError(1, "lapsum_forward_bracketed")   # LAPSUM_ERR_INVALID_ARG
+
+
 def soft_topk(scores, k, alpha, *, path: str = "auto", sample: str = "n23", z: float = 5.16,
               noise_seed: int = 0, sampler: str = "systematic", ste: bool = False):
     """Differentiable exact-budget soft top-k over the last dimension.
@@ -252,6 +265,8 @@ def soft_topk(scores, k, alpha, *, path: str = "auto", sample: str = "n23", z: f
     gradient; k must then be an integer."""
     n = scores.shape[-1]
     if path == "auto":
+        if n > _OPTIONS_MIN_N:
+            _check_bracket_options(sample, sampler, z)
         path = choose_path(n, scores.numel() // n if n else 1)
     if ste and int(float(k)) != float(k):
         raise ValueError("ste=True needs an integer k")

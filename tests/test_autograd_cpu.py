@@ -95,3 +95,23 @@ def test_missing_node_is_named_once(monkeypatch, tmp_path):
     with warnings.catch_warnings():
         warnings.simplefilter("error")
         assert not A._load_node()
+
+
+def test_bracket_options_are_checked_past_2_18():
+    """soft_topk refuses unknown bracket options for every row length that has
+    taken the bracket, whichever path "auto" takes now, and shorter rows keep
+    ignoring them."""
+    import os
+
+    import paper_2608_06912_amd as L
+    long, short = torch.zeros((1 << 18) + 1), torch.zeros(64)
+    for bad, name in (({"sample": "cube"}, "sample-size"), ({"sampler": "grid"}, "sampler")):
+        with pytest.raises(ValueError, match=name):
+            A.soft_topk(long, 4.0, -1.0, **bad)
+        with pytest.raises(ValueError, match="CUDA"):
+            A.soft_topk(short, 4.0, -1.0, **bad)
+    if os.path.exists(L.LIB_PATH):
+        for z in (0.0, -1.0, float("inf"), float("nan")):
+            with pytest.raises(L.LapsumError) as e:
+                A.soft_topk(long, 4.0, -1.0, z=z)
+            assert e.value.status == 1
