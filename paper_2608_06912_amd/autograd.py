@@ -46,10 +46,19 @@ FULL_SORT_MAX_N = 1 << 23
 FULL_SORT_MAX_N_BATCH = 1 << 22
 
 
-def choose_path(n: int, batch: int = 1) -> str:
+# Without a gradient a row costs only its forward, and the bracket no host
+# time that shows: full / bracketed, us, over nine budgets and temperatures,
+# 73 / 78 at 2^22 (49-89 / 67-86), 90 / 90 at 6e6 (59-114 / 69-105), 108 / 95
+# at 2^23 (70-140 / 73-119).
+FULL_SORT_MAX_N_FORWARD = 6_000_000
+
+
+def choose_path(n: int, batch: int = 1, grad: bool = True) -> str:
     """"full" for n <= FULL_SORT_MAX_N (FULL_SORT_MAX_N_BATCH for the rows of
-    a batch), else "bracketed"."""
-    return "full" if n <= (FULL_SORT_MAX_N if batch == 1 else FULL_SORT_MAX_N_BATCH) else "bracketed"
+    a batch, FULL_SORT_MAX_N_FORWARD for a row without a gradient), else
+    "bracketed"."""
+    most = FULL_SORT_MAX_N if grad else FULL_SORT_MAX_N_FORWARD
+    return "full" if n <= (most if batch == 1 else FULL_SORT_MAX_N_BATCH) else "bracketed"
 
 
 def sample_size(n: int, rule: str = "n23") -> int:
@@ -267,7 +276,9 @@ def soft_topk(scores, k, alpha, *, path: str = "auto", sample: str = "n23", z: f
     if path == "auto":
         if n > _OPTIONS_MIN_N:
             _check_bracket_options(sample, sampler, z)
-        path = choose_path(n, scores.numel() // n if n else 1)
+        grad = n <= FULL_SORT_MAX_N_FORWARD or torch.is_grad_enabled() and any(
+            isinstance(v, torch.Tensor) and v.requires_grad for v in (scores, k, alpha))
+        path = choose_path(n, scores.numel() // n if n else 1, grad)
     if ste and int(float(k)) != float(k):
         raise ValueError("ste=True needs an integer k")
     if path == "full":

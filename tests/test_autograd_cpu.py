@@ -41,6 +41,9 @@ def test_path_switch():
     assert A.choose_path(1) == "full"
     assert A.choose_path(A.FULL_SORT_MAX_N) == "full"
     assert A.choose_path(A.FULL_SORT_MAX_N + 1) == "bracketed"
+    assert A.choose_path(A.FULL_SORT_MAX_N_FORWARD, grad=False) == "full"
+    assert A.choose_path(A.FULL_SORT_MAX_N_FORWARD + 1, grad=False) == "bracketed"
+    assert A.choose_path(A.FULL_SORT_MAX_N_BATCH, batch=2, grad=False) == "full"
 
 
 def test_no_cpu_fallback():

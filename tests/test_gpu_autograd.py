@@ -130,3 +130,22 @@ def test_hard_topk_mask_with_ties(lib, k):
     for i in range(3):
         assert np.array_equal(m[i], _hard_mask_oracle(r[i], k)), i
         assert m[i].sum() == k
+
+
+def test_forward_only_path_equals_the_trained_one(lib):
+    """A row between the two switches: the bracket without a gradient, the full
+    path with one, the same p to float32 rounding of b."""
+    import torch
+
+    import paper_2608_06912_amd.autograd as A
+    n = A.FULL_SORT_MAX_N_FORWARD + 1001
+    assert n < A.FULL_SORT_MAX_N
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    x = torch.randn(n, generator=gen, device="cuda")
+    for k, alpha in ((0.3 * n, -0.1), (2000.0, -0.05)):
+        trained = A.soft_topk(x.requires_grad_(), k, alpha)
+        assert trained.requires_grad
+        with torch.no_grad():
+            p = A.soft_topk(x, k, alpha)
+        assert not p.requires_grad
+        assert float((p - trained.detach()).abs().max()) <= 2e-7
