@@ -55,24 +55,13 @@ def test_long_row_against_oracle(lib, n, dist):
 
 @pytest.mark.parametrize("n,frac", [((1 << 22) + 5, 0.01), ((1 << 22) + 5, 0.5), (6_000_001, 0.06)])
 def test_long_row_of_many_cells(lib, n, frac):
-    """Rows past 2^22 scores: 256 cells, merged by a launch of their own."""
+    """Rows past 2^22 scores: 256 cells, merged by a launch of their own (as
+    from 2^18 on), and up to 512 blocks."""
     rng = np.random.default_rng(n)
     for dist in ("normal", "levels", "half_zero"):
         r = _row(dist, n, rng)
         p, b = lib.lapsum_forward(_t(r), frac * n, -0.5)
         _check(r, frac * n, -0.5, _np(p), float(_np(b)[0]), (n, dist, frac))
-
-
-def test_long_row_past_the_entries_kept_on_chip(lib):
-    """One cell around the root holds most of a long row's members, more than
-    LDS keeps: scores bunched within the width of a cell."""
-    n = 3_000_001
-    rng = np.random.default_rng(5)
-    r = rng.standard_normal(n).astype(np.float32)
-    r[::3] = (1.5 + 1e-6 * rng.standard_normal(r[::3].size)).astype(np.float32)
-    for k in (0.2 * n, 0.35 * n):
-        p, b = lib.lapsum_forward(_t(r), k, -0.5)
-        _check(r, k, -0.5, _np(p), float(_np(b)[0]), k)
 
 
 @pytest.mark.parametrize("n", [70001, 3_000_001])
@@ -236,6 +225,88 @@ def _sample_positions(n, m=4096):
     x *= np.uint32(0x846ca68b)
     x ^= x >> np.uint32(16)
     return (a + ((x.astype(np.uint64) * (e - a)) >> np.uint64(32))).astype(np.int64)
+
+
+def _window_model(r, k, t):
+    """The window of a row that long_window finds, and its equal cells (64 up
+    to 2^18 scores, 256 beyond): the same sample, points and acceptance, sums
+    in float64.  None where the cells would follow the sample instead."""
+    f = np.float32
+    n, M, Z = r.size, 4096, 5.5
+    NC = 256 if n > 1 << 18 else 64
+    v = r[_sample_positions(n)].astype(np.float64)
+    mu = k * M / n
+
+    def at(x):
+        e = 0.5 * np.exp(-np.abs(v - x) / t)
+        p = np.where(v >= x, 1.0 - e, e)
+        S = p.sum()
+        var = max((p * p).sum() - S * S / M, 0.0) * mu / max(S, 1e-30)
+        return S, Z * np.sqrt(var) + Z * Z / 3.0, e.sum()
+
+    def logit(S):
+        c = min(max(S, 0.25), M - 0.25)
+        return np.log2(c / (M - c))
+
+    def between(p, Sp, q, Sq, want):
+        s = (logit(Sp) - logit(want)) / (logit(Sp) - logit(Sq))
+        x = f(p + (q - p) * min(max(s, 0.02), 0.98))
+        return x if min(p, q) < x < max(p, q) else f(0.5 * p + 0.5 * q)
+
+    mn, mx = v.min(), v.max()
+    ends = []
+    for sign, inner, outer in ((1.0, mn, mx), (-1.0, mx, mn)):   # lower end, upper end
+        (Si, mi, _), (So, _, _) = at(inner), at(outer)
+        assert sign * (Si - mu) >= mi   # (these tests' windows are bounded)
+        x = between(inner, Si, outer, So, mu + sign * 1.15 * (Z * np.sqrt(mu * (1 - mu / M)) + Z * Z / 3))
+        for it in range(1, 5):
+            S, m, F = at(x)
+            if sign * (S - mu) >= m:
+                inner, Si = x, S
+                if sign * (S - mu) <= 1.35 * m:
+                    break
+            else:
+                outer, So = x, S
+            nx = f(x + t * (S - mu - sign * 1.15 * m) / F)
+            l, h = min(inner, outer), max(inner, outer)
+            near = l < nx < h and nx >= l + 0.75 * (x - l) and nx <= h - 0.75 * (h - x)
+            x = nx if near else (between(inner, Si, outer, So, mu + sign * 1.15 * m) if it % 3
+                                 else f(0.5 * inner + 0.5 * outer))
+        else:
+            raise AssertionError("the model's points did not settle")
+        ends.append((float(inner), Si))
+    (lo, Slo), (hi, Shi) = ends
+    most = 1.25 * (Slo - Shi) / (1.0 - np.exp(-(hi - lo) / t)) * n / M
+    followed = most > 4 * 24576 or (most > 24576 and 4 * most > n)
+    edges = hi - np.arange(NC - 1) * (hi - lo) / (NC - 2)   # upper edges of cells 1 ..
+    return lo, hi, edges, followed
+
+
+@pytest.mark.parametrize("merged", [False, True])
+def test_long_row_past_the_entries_kept_on_chip(lib, merged):
+    """The cell around the root holds more entries than LDS keeps, in a window
+    too small for the cells to follow the sample: thousands of distinct scores
+    within the width of one cell; with a value met often elsewhere in the
+    window (a merged cell, whose weights halve what LDS keeps)."""
+    n = 500_000
+    rng = np.random.default_rng(5)
+    r = rng.standard_normal(n).astype(np.float32)
+    part = n // 25 if merged else n // 15
+    r[:part] = (1e-5 * rng.standard_normal(part)).astype(np.float32)
+    if merged:
+        r[part:part + n // 100] = np.float32(0.05)
+    r = rng.permutation(r)
+    k = float(O.lapsum(r, 0.0, 0.06))
+    lo, hi, edges, followed = _window_model(r, k, 0.06)
+    assert lo < -1e-4 and hi > 1e-4 and not followed
+    c = int(np.searchsorted(-edges, 0.0)) - 1   # the cell of b = 0
+    top, bottom = edges[max(c - 1, 0)], edges[min(c + 2, edges.size - 1)]
+    held = int(np.count_nonzero((r < top) & (r >= bottom)))
+    assert held > (24576 // 2 if merged else 24576) + 2000, held
+    if merged:
+        assert lo < 0.05 < hi
+    p, b = lib.lapsum_forward(_t(r), k, -0.06)
+    _check(r, k, -0.06, _np(p), float(_np(b)[0]), merged)
 
 
 @pytest.mark.parametrize("n", [50001, 1_500_001])
