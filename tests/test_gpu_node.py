@@ -130,31 +130,32 @@ def test_native_node_reports_each_failure_as_its_own(lib):
 
 def test_native_node_runs_without_the_gil(lib):
     """Another Python thread gets to run while the forward is in native code
-    (no thread is made to yield here, so only the call itself can)."""
+    (no thread is made to yield here, so only the call itself can): in most of
+    the calls, against one of 60 where the call keeps the GIL."""
     import sys
     import threading
 
     import torch
 
     import paper_2608_06912_amd.autograd as A
-    x = torch.randn(256, 4096, device="cuda")
+    x = torch.randn(4096, 4096, device="cuda")
     A.soft_topk(x, 10.0, -1.0)
-    ran = []
+    ran = 0
     old = sys.getswitchinterval()
     try:
-        for _ in range(500):
+        for _ in range(60):
             go = threading.Event()
             seen = []
             t = threading.Thread(target=lambda: (go.wait(), seen.append(1)))
             t.start()
+            torch.cuda.synchronize()
+            torch.cuda.empty_cache()   # (so that the forward allocates)
             sys.setswitchinterval(1000.0)
             go.set()
             A._native_full(x, 10.0, -1.0)
-            ran = list(seen)
+            ran += len(seen)
             sys.setswitchinterval(old)
             t.join()
-            if ran:
-                break
     finally:
         sys.setswitchinterval(old)
-    assert ran
+    assert ran >= 30, ran
