@@ -33,7 +33,8 @@ from . import (HERE, LapsumError, lapsum_backward, lapsum_backward_band, lapsum_
 __all__ = ["soft_topk", "hard_topk_mask", "straight_through", "choose_path", "sample_size",
            "bracket_noise", "bracket_indices", "LapSumFunction", "FULL_SORT_MAX_N"]
 
-# A row up to this length takes the full path; longer rows the sample bracket.
+# A row up to this length takes the full path (which sorts only for a
+# permutation; the names are older); longer rows the sample bracket.
 # §4 places the switch where the two paths cost the same.  On MI355X, forward
 # + backward of one Gaussian row, full against bracket: 0.12 / 0.17 ms at
 # n = 2^18 .. 2^22 (both host-bound), 0.14 / 0.19 at 2^23 and 0.23 / 0.21 at
@@ -267,11 +268,11 @@ def soft_topk(scores, k, alpha, *, path: str = "auto", sample: str = "n23", z: f
               noise_seed: int = 0, sampler: str = "systematic", ste: bool = False):
     """Differentiable exact-budget soft top-k over the last dimension.
 
-    path: "full" (sort), "bracketed" (sample bracket, §4) or "auto"
-    (choose_path by row length).  sample: the bracket's sample-size rule
-    (sample_size); sampler: "systematic" (§4's strided view) or "iid"
-    (uniform indices, the coverage theorem's model).  ste=True returns the hard mask with the soft p's
-    gradient; k must then be an integer."""
+    path: "full" (one threshold solve per row), "bracketed" (sample bracket,
+    §4) or "auto" (choose_path by row length).  sample: the bracket's
+    sample-size rule (sample_size); sampler: "systematic" (§4's strided view)
+    or "iid" (uniform indices, the coverage theorem's model).  ste=True returns
+    the hard mask with the soft p's gradient; k must then be an integer."""
     n = scores.shape[-1]
     if path == "auto":
         if n > _OPTIONS_MIN_N:

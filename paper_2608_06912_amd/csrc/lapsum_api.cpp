@@ -127,7 +127,9 @@ FullWs carve_full(Carve& c, int64_t batch, int64_t n, bool with_vals) {
   w.sb.hist = c.take<uint32_t>(sort_hist_words(n));
   w.sb.totals = c.take<uint32_t>(256);
   w.sb.max_tiles = sort_max_tiles(n);
-  // (room that the size of a row's workspace has always counted)
+  // (more than the solve needs without the permutation: the size, and with it
+  // the row lengths that lapsum_forward_noalloc accepts and refuses, stays
+  // what the header says)
   c.take<double>(static_cast<size_t>(tiles_of(n) < 1 ? 1 : tiles_of(n)) * kSolveTileDoubles);
   c.take<SolveRec>(1);
   // the solve works in the same memory, after the sort
@@ -649,11 +651,11 @@ const char* lapsum_status_string(int status) {
   }
 }
 
-// One workgroup per row sorts rows of up to kRowOnChipMax scores on chip,
+// One workgroup per row solves rows of up to kRowOnChipMax scores on chip,
 // all rows of a batch at once.  A single row longer than kRowSingleMax
-// leaves most of the chip idle that way and goes through the device-wide
-// sort instead (measured on MI355X: n = 32768 alone takes 0.122 ms on one
-// workgroup against 0.072 ms device-wide; at 16384 the two are even).
+// leaves most of the chip idle that way and goes through the long rows' solve
+// instead (kernels on MI355X: n = 32768 alone 57 us on one workgroup against
+// 44, 24576 50 against 41; at 16384 the two are even, 40 and 41).
 constexpr int64_t kRowSingleMax = 16384;
 
 bool forward_on_chip(int64_t batch, int64_t n) {

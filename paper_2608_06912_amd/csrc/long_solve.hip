@@ -2,12 +2,14 @@
 // rows at a time (used for every row that one workgroup does not hold on
 // chip; the sort remains for the permutation).
 //
-// Three launches, one row per grid.y:
+// Three launches, four past 2^18 scores (long_merge), one row per grid.y:
 //   long_window   one workgroup per row: a stratified random sample of the
-//                 row (4096 scores) gives a window [xlo, xhi) that
-//                 holds b except with a probability of about 1e-7: LapSum of
-//                 the sample, less (plus) a Bernstein margin, still lies
-//                 above (below) the budget at its ends
+//                 row (4096 scores, 16384 past 2^24) gives a window [xlo, xhi)
+//                 that holds b in all but about 2 e^{-z^2/2} = 5e-7 of samples
+//                 (z = 5.5; for independent positions and a known variance,
+//                 an estimate here): LapSum of the sample, less (plus) a
+//                 Bernstein margin, still lies above (below) the budget at its
+//                 ends
 //   long_pass     the one streaming pass over the row: scores at or above
 //                 xhi and below xlo are summed as the tails of Suppl. B, the
 //                 members of the window are sorted into cells (count, the two
@@ -16,9 +18,10 @@
 //                 every cell edge, and the members of the cell that holds b
 //                 and of its two neighbours narrowed down to the root
 //                 (narrow.hpp).  The tails give LapSum at the window's ends
-//                 exactly; a row whose root lies outside its window, or
-//                 whose cells hold too many scores, is narrowed over the
-//                 whole row by this workgroup (slow, and always right).
+//                 exactly; where the root lies outside them, the whole row
+//                 is divided and narrowed by this workgroup, and where the
+//                 three cells hold more than LDS, their entries are (slower,
+//                 and always right).
 // The sample decides only which scores are looked at one by one: b is the
 // root of the same equation, from the sums of every score.
 //
@@ -41,9 +44,9 @@ namespace {
 // One wave per SIMD in the latency-bound kernels: what every wave computes
 // for itself (the sums over the waves' partials, the carries) is issued once
 // per SIMD instead of four times (1024 threads: 1.7 us a point of long_window
-// and 6 us a point of long_root, against 0.6 and 0.9).
+// and 6 us a point of long_root, against 0.7 and 0.9).
 constexpr int WT = 256;
-constexpr int MT = 1024;   // long_root threads while it merges the blocks' cells
+constexpr int MT = 1024;   // long_root threads while it merges or divides cells
 constexpr int LT = 512;    // long_pass threads
 constexpr int LW = LT / kWave;
 constexpr int kStage = 512;               // members a wave of long_pass stages
@@ -67,8 +70,11 @@ struct Window {
 // Where equal steps would leave one cell with most of the members (many equal
 // scores, clusters, a sentinel inside the window), the cells follow the
 // sample instead: bound[c], non-increasing, is the least score of cell c for
-// c < NC - 1, every bound the same share of the sample's members apart; a
-// value met by several bounds has a cell to itself (see long_window).
+// c < NC - 1, every bound the same share of the sample's members apart (one
+// row of 1e6 scores, forward, us, equal steps / by the sample: two clusters
+// 18000 / 260, 30% of the scores -3.4e38 and k = 0.69 n 4800 / 120, a third of
+// the row 1e-6 wide 1700 / 95; the sort 70-160); a value met by several
+// bounds has a cell to itself (see long_window).
 template <int NC>
 __device__ __forceinline__ int cell_of(const Window& w, float v) {
   if (v > w.xcap) return 0;
@@ -124,6 +130,9 @@ struct LongCells {
   uint32_t* mcnt;
 };
 
+// Chris Wellons' 32-bit mixer "lowbias32" (its shifts and two multipliers, from
+// his search for integer hashes of low bias, "hash prospector", 2018): every
+// input bit flips every output bit in close to half of the cases.
 __device__ __forceinline__ uint32_t mix32(uint32_t x) {
   x ^= x >> 16;
   x *= 0x7feb352du;
@@ -426,8 +435,8 @@ __global__ __launch_bounds__(WT) void long_window_kernel(const float* __restrict
 
 // ------------------------------------------------------------------ pass ---
 // Block g streams scores [g chunk, (g + 1) chunk) of its row.  One
-// exponential per score, for whichever tail holds it.  Members are staged per wave in LDS, then summed into the
-// cells by LDS atomics (64-bit fixed point: integer additions commute) and
+// exponential per score, for whichever tail holds it.  Members are staged per
+// wave in LDS, then summed into the cells by LDS atomics (64-bit fixed point: integer additions commute) and
 // written out in cell order.  A cell whose members are all equal (quantised
 // scores) is written as one entry.  A block whose members outgrow the staging
 // streams its chunk twice more instead (from the caches): once for the cells,
@@ -823,7 +832,9 @@ __device__ void root_cell(const uint32_t* cn, const double* lap, double k, int* 
 // sample of the row's scores in their range, one pass over the entries for the
 // cells' sums, one to collect those of the root's cell and its neighbours in
 // LDS.  A cell of equal entries is collected as one.  Two passes of 16 waves
-// instead of one of four waves for each of 10 to 20 points.  (The sample is
+// instead of one of four waves for each of 10 to 20 points (1e6 scores of
+// which 1% are -3.4e38, k = 0.99 n, forward: 2300 -> 150 us; two passes of
+// four waves 300).  (The sample is
 // the row's and not the entries', whose order in a list is not always the
 // same: every call takes the same cells.)
 constexpr int kSub = 256;

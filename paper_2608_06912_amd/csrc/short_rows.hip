@@ -11,7 +11,7 @@
 //
 // Bound: vector issue, about 200 instructions per point and wave at four
 // scores per lane (half of them the float64 sums over the wave) and five to
-// eight points.  4096 rows of 256 scores (k = 16, t = 1): 140 -> 11 us.  At
+// eight points.  4096 rows of 256 scores (k = 8, t = 1): 140 -> 18 us.  At
 // t = 0.02 the start and the proportional points took 256 rows of 256 with
 // k = 0.26 from 24.5 to 15.2 us (backward included, bisection before).  Rows
 // with a sentinel among the scores (-3.4e38, -1e9) take 9-15 points; without

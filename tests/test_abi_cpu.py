@@ -50,7 +50,7 @@ def test_workspace_sizes():
     # rows that fit on chip need no workspace
     assert L.lapsum_forward_workspace_size(256, 32768) == 0
     assert L.lapsum_forward_workspace_size(1, 16384) == 0
-    # one row longer than 16384 goes through the device-wide sort
+    # one row longer than 16384 goes through the long rows' device-wide solve
     assert L.lapsum_forward_workspace_size(1, 32768) > 0
     assert L.lapsum_forward_workspace_size(2, 32768) == 0
     assert L.lapsum_backward_workspace_size(256, 32768) == 0
