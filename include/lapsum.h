@@ -86,8 +86,9 @@ const char* lapsum_status_string(int status);
  * except a batch of one row longer than 16384.  That row and all longer ones
  * are solved device-wide, several rows at a time, without sorting: a sample
  * gives a window that holds b, one pass sums the scores outside it and keeps
- * those inside, and the members around the root give the same b as the sort
- * (they are sorted only for perm_out, one row after another).  The workspace
+ * those inside, and the members around the root give b.  For perm_out they
+ * are sorted, one row after another, and b may come from the order: the root
+ * of the same equation, equal up to the rounding of its sums.  The workspace
  * size depends on batch for both reasons; it does not exceed the larger of
  * one row's and 48 MiB.
  * ------------------------------------------------------------------------ */

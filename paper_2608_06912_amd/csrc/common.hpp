@@ -110,6 +110,13 @@ __device__ __forceinline__ double exp2_neg(double y) {
   return ldexp(r, static_cast<int>(n));
 }
 
+// A per-score term in float32 or, F64, to the accuracy of exp2_neg.
+template <bool F64>
+__device__ __forceinline__ double wexp_term(double d, double c2) {
+  if constexpr (F64) return exp2_neg(-d * c2);
+  else return wexp_f32(d, c2);
+}
+
 // Laplace(0, t) draw number s of the bracket's default kernel noise (the
 // sample takes it when the caller passes no table).  A counter-based
 // generator, so the same (seed, s) always gives the same draw and no state
@@ -493,7 +500,7 @@ __device__ inline double gap_root(double k, double t, double c_up, bool has_up, 
 // known to hold the crossing, or b lies between the block's first score and
 // whatever precedes it.  Returns b (the same value in every thread) and the
 // block totals ext_pre (+) block, block (+) ext_suf.
-template <int BLOCK, int ITEMS>
+template <int BLOCK, int ITEMS, bool F64 = false>
 __device__ double block_solve(const float (&s)[ITEMS], int cnt, double rank0, Pre ext_pre,
                               Suf ext_suf, double k, double t, ScanSmem<BLOCK / kWave>& sm,
                               Pre* pre_total, Suf* suf_total) {
@@ -518,8 +525,8 @@ __device__ double block_solve(const float (&s)[ITEMS], int cnt, double rank0, Pr
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
       if (i < cnt) {
-        sp += wexp_f32(static_cast<double>(s[i]) - last, c2);
-        if (i > 0) suf_x += wexp_f32(first - static_cast<double>(s[i]), c2);
+        sp += wexp_term<F64>(static_cast<double>(s[i]) - last, c2);
+        if (i > 0) suf_x += wexp_term<F64>(first - static_cast<double>(s[i]), c2);
       }
     }
     mine_pre = Pre{lastf, sp};
@@ -578,7 +585,7 @@ __device__ double block_solve(const float (&s)[ITEMS], int cnt, double rank0, Pr
       if (pc.S != 0.0) P += wexp_f64(static_cast<double>(pc.u) - si, inv_t) * pc.S;
       if (sc.T != 0.0) E += wexp_f64(si - static_cast<double>(sc.v), inv_t) * sc.T;
       // the run's own terms are per-score terms like those of the group
-      // summaries (float32 exponentials of float64 differences), unrolled
+      // summaries (exponentials of float64 differences), unrolled
       // over the run's capacity so that they are all independent (runs of
       // 32 keep the loop: their kernels are short of registers already)
       double Pt = 0.0, Et = 0.0;
@@ -587,15 +594,15 @@ __device__ double block_solve(const float (&s)[ITEMS], int cnt, double rank0, Pr
         for (int j = 0; j < ITEMS; ++j) {
           if (j < oc) {
             const double sj = sm.sv[j];
-            if (j < tid) Pt += wexp_f32(sj - si, c2);
-            else if (j > tid) Et += wexp_f32(si - sj, c2);
+            if (j < tid) Pt += wexp_term<F64>(sj - si, c2);
+            else if (j > tid) Et += wexp_term<F64>(si - sj, c2);
           }
         }
       } else {
         for (int j = 0; j < oc; ++j) {
           const double sj = sm.sv[j];
-          if (j < tid) Pt += wexp_f32(sj - si, c2);
-          else if (j > tid) Et += wexp_f32(si - sj, c2);
+          if (j < tid) Pt += wexp_term<F64>(sj - si, c2);
+          else if (j > tid) Et += wexp_term<F64>(si - sj, c2);
         }
       }
       P += Pt;

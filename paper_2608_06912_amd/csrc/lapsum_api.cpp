@@ -115,7 +115,10 @@ int check_ws(void* ws, size_t have, size_t need) {
 // ------------------------------------------------------------- long rows --
 struct FullWs {
   void* base;       // the long rows' solve works from here
-  SortBuffers sb;   // the permutation's sort, before the solve
+  SortBuffers sb;   // or the permutation's sort here, and the solve of its order
+  int64_t solve_tiles;
+  double* tile_buf;
+  SolveRec* rec;
 };
 
 FullWs carve_full(Carve& c, int64_t batch, int64_t n, bool with_vals) {
@@ -127,12 +130,12 @@ FullWs carve_full(Carve& c, int64_t batch, int64_t n, bool with_vals) {
   w.sb.hist = c.take<uint32_t>(sort_hist_words(n));
   w.sb.totals = c.take<uint32_t>(256);
   w.sb.max_tiles = sort_max_tiles(n);
-  // (more than the solve needs without the permutation: the size, and with it
-  // the row lengths that lapsum_forward_noalloc accepts and refuses, stays
-  // what the header says)
-  c.take<double>(static_cast<size_t>(tiles_of(n) < 1 ? 1 : tiles_of(n)) * kSolveTileDoubles);
-  c.take<SolveRec>(1);
-  // the solve works in the same memory, after the sort
+  w.solve_tiles = tiles_of(n) < 1 ? 1 : tiles_of(n);
+  w.tile_buf = c.take<double>(static_cast<size_t>(w.solve_tiles) * kSolveTileDoubles);
+  w.rec = c.take<SolveRec>(1);
+  // without the permutation the solve takes the same memory, which is more
+  // than it needs: the size, and with it the row lengths that
+  // lapsum_forward_noalloc accepts and refuses, stays what the header says
   const size_t need = long_solve_bytes(long_rows(batch, n), n);
   if (c.size() < need) c.take<char>(need - c.off);
   w.base = w.sb.keys[0];
@@ -715,16 +718,40 @@ int lapsum_forward(const float* scores, int64_t batch, int64_t n, double k, doub
   }
   Carve c(workspace);
   FullWs w = carve_full(c, batch, n, perm_out != nullptr);
-  // the sort first: p may be written over the scores
-  for (int64_t row = 0; perm_out && row < batch; ++row) {
+  if (!perm_out) return long_forward(scores, batch, n, k, t, p, b, w.base, stream);
+  // A row sorted for its permutation is solved from its order; the shorter rows
+  // of a batch together by the long rows' solve, whose launches serve them all
+  // (forward, us, order / long rows' solve: one row of 2e5 73 / 83, of 1e6 94 /
+  // 118, of 4e6 177 / 211; four rows 274 / 232, 361 / 326, 704 / 724).  p comes
+  // last: it may be written over the scores.
+  const bool from_order = batch == 1 || n > (int64_t(1) << 21);
+  for (int64_t row = 0; row < batch; ++row) {
     const uint32_t* keys = nullptr;
     const int32_t* vals = nullptr;
     LAPSUM_TRY(launch_sort(scores + row * n, nullptr, nullptr, true, n, nullptr, w.sb, 0xfu, &keys,
                            &vals, stream));
+    if (from_order) {
+      SolveArgs a{};
+      a.keys = keys;
+      a.len = n;
+      a.k = k;
+      a.t = t;
+      a.n_total = n;
+      a.tile_buf = w.tile_buf;
+      a.max_tiles = w.solve_tiles;
+      a.out = w.rec;
+      a.b_out = b + row;
+      LAPSUM_TRY(launch_sorted_solve(a, stream));
+    }
     LAPSUM_TRY(hipMemcpyAsync(perm_out + row * n, vals, static_cast<size_t>(n) * sizeof(int32_t),
                               hipMemcpyDeviceToDevice, stream));
   }
-  return long_forward(scores, batch, n, k, t, p, b, w.base, stream);
+  if (!from_order) return long_forward(scores, batch, n, k, t, p, b, w.base, stream);
+  for (int64_t row = 0; row < batch; row += 65535) {
+    const int64_t rows = batch - row < 65535 ? batch - row : 65535;
+    LAPSUM_TRY(launch_emit(scores + row * n, rows, n, b + row, t, p + row * n, stream));
+  }
+  return LAPSUM_OK;
 }
 
 // Long rows of the backward launched together (one grid.y each), with the

@@ -99,8 +99,8 @@ __global__ __launch_bounds__(TT) void solve_tiles_kernel(const uint32_t* __restr
   for (int i = 0; i < TI; ++i) {
     if (static_cast<int64_t>(tid) * TI + i < nv) {
       const double s = key_float(kv[i]);
-      S += wexp_f32(s - last, c2);
-      if (tid * TI + i > 0) X += wexp_f32(first - s, c2);
+      S += exp2_neg((last - s) * c2);
+      if (tid * TI + i > 0) X += exp2_neg((s - first) * c2);
     }
   }
   S = wave_sum(S);
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(TT) void solve_finalize_kernel(SolveArgs a, double*
       s[i] = (i < cnt) ? key_float(a.keys[base + static_cast<int64_t>(tid) * TI + i]) : 0.0f;
     Pre pt;
     Suf st;
-    b = block_solve<TT, TI>(s, cnt, x.nR + static_cast<double>(base), tp, ts, k, t, sm, &pt, &st);
+    b = block_solve<TT, TI, true>(s, cnt, x.nR + static_cast<double>(base), tp, ts, k, t, sm, &pt, &st);
   }
   if (tid == 0) {
     rec.b = b;
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(FT) void solve_finalize_wide_kernel(SolveArgs a, do
       sv[i] = (i < cnt) ? key_float(a.keys[base + static_cast<int64_t>(tid) * FTI + i]) : 0.0f;
     Pre pt;
     Suf st;
-    b = block_solve<FT, FTI>(sv, cnt, x.nR + static_cast<double>(base), tp, ts, k, t, sm, &pt, &st);
+    b = block_solve<FT, FTI, true>(sv, cnt, x.nR + static_cast<double>(base), tp, ts, k, t, sm, &pt, &st);
   }
   if (tid == 0) {
     rec.b = b;

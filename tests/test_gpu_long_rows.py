@@ -214,6 +214,29 @@ def test_long_row_with_crowded_cells(lib, n, layout, kf, alpha):
     assert ms <= 12.0 * ref, (n, layout, kf, alpha, ms, ref)
 
 
+@pytest.mark.parametrize("batch,n", [(1, 16385), (1, 70_001), (3, 70_001), (1, 1_000_003),
+                                     (2, (1 << 21) + 5), (2, 1 << 21)])
+def test_long_row_with_its_order(lib, batch, n):
+    """With the permutation a long row is solved from its order, or with the
+    batch: b as without it to 1e-10 t (both are right to 4e-12 t)."""
+    rng = np.random.default_rng([batch, n, 7])
+    r = np.stack([_row(("normal", "levels", "outliers")[i % 3], n, rng) for i in range(batch)])
+    x = _t(r)
+    for k, alpha in ((0.05 * n, -1.0), (16.0, -0.5), (0.3 * n, -0.01)):
+        p, b, perm = lib.lapsum_forward(x, k, alpha, perm=True)
+        p0, b0 = lib.lapsum_forward(x, k, alpha)
+        b, b0 = _np(b), _np(b0)
+        for i in range(batch):
+            assert abs(b[i] - b0[i]) <= 1e-10 * -alpha + 4e-16 * abs(b0[i]), (n, i, k, alpha)
+            assert np.array_equal(_np(perm[i]), O.desc_order(r[i]))
+        assert float((p - p0).abs().max()) <= P_TOL
+    # one row's order is not solved a second time without it
+    lib.lapsum_profile_start()
+    lib.lapsum_forward(x, 0.05 * n, -1.0, perm=True)
+    names = set(lib.lapsum_profile_stop())
+    assert ("long_window" in names) == (batch > 1 and n <= 1 << 21), names
+
+
 def _sample_positions(n, m=4096):
     """Where the window's sample reads (one hashed position per stratum)."""
     s = np.arange(m, dtype=np.uint64)
