@@ -82,3 +82,31 @@ def test_hard_mask_of_many_groups(lib):
     assert bool((m.sum(1) == k).all())
     ref = torch.zeros_like(x).scatter_(1, torch.sort(x, dim=1, descending=True, stable=True)[1][:, :k], 1.0)
     assert bool((m == ref).all())
+
+
+@pytest.mark.parametrize("batch,n", [(5, 300), (3, 4096), (2, 20001), (3, 40003)])
+def test_hard_mask_under_graph_capture(lib, batch, n):
+    """Captured once and replayed on new scores, with eager work between: every
+    replay equals the eager mask (the histograms are cleared by a kernel)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(batch, n, generator=gen, device="cuda")
+    k = n // 7
+    ws = torch.empty(lib.lapsum_hard_mask_workspace_size(batch, n), dtype=torch.uint8, device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        lib.lapsum_hard_mask(x, k, workspace=ws)
+    torch.cuda.current_stream().wait_stream(s)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        m = lib.lapsum_hard_mask(x, k, workspace=ws)
+    for i in range(4):
+        x.copy_(torch.randn(batch, n, generator=gen, device="cuda") if i != 2 else
+                torch.randint(-2, 3, (batch, n), generator=gen, device="cuda").float())
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = m.clone()
+        assert torch.equal(got, lib.lapsum_hard_mask(x, k))
