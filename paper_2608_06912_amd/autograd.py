@@ -222,6 +222,7 @@ def _native_full(scores, k, alpha, ste=False):
             or (at and type(alpha) not in _PLAIN) or not scores.is_cuda
             or scores.layout is not torch.strided or scores.numel() == 0
             or scores.is_complex() or scores.is_quantized
+            or (kt and k.numel() != 1) or (at and alpha.numel() != 1)
             or torch.compiler.is_compiling()
             or torch._C._len_torch_function_stack() or torch._C._len_torch_dispatch_stack()
             or torch._C._are_functorch_transforms_active()

@@ -76,6 +76,9 @@ def test_native_node_leaves_transforms_and_errors_to_the_python_node(lib):
         with pytest.raises(lib.LapsumError) as e:
             A.soft_topk(x, k, alpha)
         assert e.value.status == 1
+    for k, alpha in ((torch.tensor([1.0, 2.0]), -1.0), (10.0, torch.tensor([-1.0, -2.0], device="cuda"))):
+        with pytest.raises(ValueError, match="one element"):
+            A.soft_topk(x, k, alpha)
     packed = []
     with torch.autograd.graph.saved_tensors_hooks(lambda t: packed.append(t.shape) or t, lambda t: t):
         A.soft_topk(x.requires_grad_(), 10.0, -1.0).sum().backward()
