@@ -14,7 +14,7 @@
 // eight points.  4096 rows of 256 scores (k = 8, t = 1): 140 -> 18 us.  At
 // t = 0.02 the start and the proportional points took 256 rows of 256 with
 // k = 0.26 from 24.5 to 15.2 us (backward included, bisection before).  Rows
-// with a sentinel among the scores (-3.4e38, -1e9) take 9-15 points; without
+// with a sentinel among the scores (-3.4e38, -1e9) take 8-15 points; without
 // the middles of the keys 25-40 (4096 rows of 200, 30% masked, forward, us:
 // 49-82, with them 25-33, plain rows 20; the 2048 buckets 120-170).
 #include <math.h>
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(RT) void row_wave_forward_kernel(const float* __res
   double flo = n, fhi = 0.0;   // LapSum at the ends (about, until they are points)
   int same = 0, last = 0;
   uint32_t left = static_cast<uint32_t>(n);
-  bool key = false;   // the last point was a middle of the keys
+  uint32_t stuck = 0u;   // points in a row that left nearly every score between the ends
   for (int it = 0; it < 96; ++it) {
     const double xd = x;
     double P = 0.0, E = 0.0;
@@ -102,9 +102,11 @@ __global__ __launch_bounds__(RT) void row_wave_forward_kernel(const float* __res
     const double F = 0.5 * (P + E);
     if (it < 12 && F > 0.0)
       xn = static_cast<float>(xd + t * (f - k) / F * static_cast<double>(1 << (same < 6 ? same : 6)));
-    if (left <= 4u && !(xn > lo && xn < hi)) {
-      // few scores left and no Newton step: one of them, which settles it and
-      // all on one side of it
+    if (it >= 3) stuck = left > old - old / 10u ? stuck + 1u : 0u;
+    if ((left <= 4u && !(xn > lo && xn < hi)) || (stuck != 0u && (stuck & 3u) == 0u)) {
+      // few scores left and no Newton step, or many equal ones that no point
+      // between the ends parts: one of them, which settles it and all on one
+      // side of it
       float m = -INFINITY;
 #pragma unroll
       for (int i = 0; i < ITEMS; ++i) m = fmaxf(m, (v[i] > lo) & (v[i] < hi) ? v[i] : -INFINITY);
@@ -118,12 +120,9 @@ __global__ __launch_bounds__(RT) void row_wave_forward_kernel(const float* __res
       xn = l + (h - l) * fminf(fmaxf(s, 0.05f), 0.95f);
     }
     if (!(xn > lo && xn < hi)) xn = middle(fmaxf(lo, mn), fminf(hi, mx), it);
-    if (it >= 3 && left > 4u) {
-      // a point that left nearly every score between the ends is followed by
-      // the middle of the keys: rows masked with a sentinel, heavy tails
-      key = !key && left > old - old / 10u;
-      if (key) xn = key_mid(fmaxf(lo, mn), fminf(hi, mx));
-    }
+    // after a point that left nearly every score between the ends, the middle
+    // of the keys: rows masked with a sentinel, heavy tails
+    if ((stuck & 1u) != 0u && left > 4u) xn = key_mid(fmaxf(lo, mn), fminf(hi, mx));
     if (!(xn > lo && xn < hi)) xn = key_mid(lo, hi);
     x = xn;
     if (!(x > lo && x < hi)) break;   // no float between the ends

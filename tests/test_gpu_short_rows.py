@@ -61,3 +61,5 @@ def test_masked_short_rows(lib, batch, n, low):
             assert abs(b[i] - ref) <= 2e-8 * -alpha + 4e-16 * abs(ref), (i, k, alpha)
             assert np.max(np.abs(p[i].astype(np.float64) - O.probs(x[i], ref, alpha))) <= 2e-7
         assert ms(xt, k, alpha) <= 2.5 * ms(pt, k, alpha), (k, alpha)
+    # near the unmasked count, where b of many rows lies at the sentinel itself
+    assert ms(xt, 0.69 * n, -0.05) <= 3.0 * ms(pt, 0.69 * n, -0.05)
