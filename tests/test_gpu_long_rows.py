@@ -214,6 +214,22 @@ def test_long_row_with_crowded_cells(lib, n, layout, kf, alpha):
     assert ms <= 12.0 * ref, (n, layout, kf, alpha, ms, ref)
 
 
+@pytest.mark.parametrize("layout,kf", [("zeros", 0.674), ("masked", 0.69), ("narrow", 0.5)])
+def test_bracket_that_falls_back_on_a_crowded_row(lib, layout, kf):
+    """Rows whose bracket holds too many scores end in the long rows' solve (5 s
+    for one row of 1e8 with 30% masked, before its cells were divided)."""
+    n = 12_000_000
+    r = _crowded(layout, n)
+    x, plain = _t(r), _t(_crowded("plain", n))
+    k, alpha = kf * n, -0.05
+    p, b, info, _ = lib.lapsum_forward_bracketed(x, k, alpha, None, K=52415)
+    _check_equation(r, k, alpha, _np(p), float(_np(b)[0]), (layout, info))
+    assert info[0]["fell_back"] == 1 or layout == "masked", (layout, info)
+    ms = _ms(lambda: lib.lapsum_forward_bracketed(x, k, alpha, None, K=52415), 3)
+    ref = _ms(lambda: lib.lapsum_forward_bracketed(plain, k, alpha, None, K=52415), 3)
+    assert ms <= 12.0 * ref, (layout, info, ms, ref)
+
+
 @pytest.mark.parametrize("batch,n", [(1, 16385), (1, 70_001), (3, 70_001), (1, 1_000_003),
                                      (2, (1 << 21) + 5), (2, 1 << 21)])
 def test_long_row_with_its_order(lib, batch, n):
