@@ -161,11 +161,11 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
 // of magnitude (scores masked with a sentinel, heavy tails): from the fifth
 // point on, one that leaves more than three quarters of the samples between
 // the ends is followed by the middle of the keys, which is sensitive to
-// magnitudes.  Rows with 30% of the scores at -3.4e38 take 7-12 points instead
-// of the last; bell-shaped and exponential rows, 2-6 of which settle, as many as without
-// it (from the third point on exponential ones took up to 9).  Where no point qualifies
-// after kWindowPoints, the ends are what they are: the cells
-// (and not b) depend on them.
+// magnitudes.  Rows with 30% of the scores at -3.4e38 take 7-12 points, without
+// it all 28 that there were; bell-shaped and exponential rows take 2-6 as
+// before (taken from the third point on, exponential ones took up to 9).
+// Where no point qualifies after kWindowPoints, the ends are what they are:
+// the cells (and not b) depend on them.
 // Each point costs about 0.7 us of one workgroup's latency: the start by the
 // logit instead of in the middle takes three points instead of four to six
 // (kernel 13.5 -> 12.8 us at 1e6 scores, 15.6 -> 13.3 for 48 rows of 131073).
@@ -359,12 +359,13 @@ __global__ __launch_bounds__(WT) void long_window_kernel(const float* __restrict
   if (!(w.scale < INFINITY)) w.scale = 0.0f;
   w.x0 = 0.5f * w.xcap + 0.5f * w.xfloor;
   // the cells by the sample where equal steps would crowd three neighbouring
-  // ones past what long_root keeps on chip, several times their share.  Looked
-  // at where the window can hold a quarter of the row or four times as much
-  // as that (below, long_root divides a crowded cell itself, in 0.1-0.2 ms; the
-  // look costs 1.5 us, which ordinary rows with wide windows would pay).  A
-  // member's term differs between the ends by (1 - e^{-width/t})/2 next to
-  // one of them up to nearly 1 halfway, which tells about how many there are.
+  // ones past what long_root keeps on chip, several times their share.  The
+  // sample is looked at where the window can hold a quarter of the row, or
+  // four times what long_root keeps (with fewer members long_root divides a
+  // crowded cell itself, in 0.1-0.2 ms; the look costs 1.5 us, which ordinary
+  // rows with wide windows would pay).  A member's term differs between the
+  // ends by (1 - e^{-width/t})/2 next to one of them up to nearly 1 halfway,
+  // which tells about how many there are.
   auto member = [&](float x) { return x >= w.xlo && x < w.xhi; };
   const float per = static_cast<float>(static_cast<double>(n) / M);   // scores per sample
   const float ends = fminf(mx, w.xhi) - fmaxf(mn, w.xlo);
